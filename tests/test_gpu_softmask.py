@@ -259,6 +259,21 @@ def test_tuner_at_and_beyond_the_lds_statistics_limit(B):
     assert mask == oracle.harden(lt.cpu().numpy(), 6)
 
 
+@pytest.mark.parametrize("B", [1, 63, 64, 65, 129, 256, 257])
+def test_tuner_at_the_edges_of_its_groups_of_64_images(B):
+    # one, two and four groups of energies in registers, and any number read
+    # again every step; single images alone in a row, a wave and a group
+    x = _images(B, 8, 16)
+    l0 = _logits(4)
+    steps, lr = 8, 0.05
+    lt, trace, mask = sm.tune(x.cuda(), _dev(l0), steps=steps, lr=lr, n_private=6)
+    lref, tref = oracle.softmask_adam(x.double().numpy(), l0.astype(np.float64), steps, lr)
+    tr = trace.cpu().numpy()
+    assert np.all(np.abs(tr - tref) <= 1e-5 * np.abs(tref))
+    assert np.abs(lt.cpu().numpy() - lref).max() <= 1e-4
+    assert mask == oracle.harden(lt.cpu().numpy(), 6)
+
+
 def test_shape_errors():
     x = torch.zeros((1, 12, 16), dtype=torch.float32, device="cuda")
     with pytest.raises(sf.SefragError) as e:
