@@ -164,6 +164,28 @@ def test_encrypt_private_matches_oracle(nbytes, first):
     assert np.array_equal(out.cpu().numpy(), data)
 
 
+@pytest.mark.parametrize("low", [bytes(8), bytes(5) + b"\xff\xfe\x00", b"\xff" * 5 + b"\xfe\x00\x01"])
+@pytest.mark.parametrize("nbytes", [(4 << 20) - 16, 4 << 20, (4 << 20) + 5])
+def test_encrypt_private_with_workgroup_wide_tables(nbytes, low):
+    # the kernels on either side of 4 MiB; counters that carry out of 16 bits,
+    # out of the low 64 and (first_block near 2^64) back again
+    rng = np.random.default_rng(nbytes)
+    key = rng.integers(0, 256, 16, dtype=np.uint8).tobytes()
+    ctr0 = bytes(7) + b"\x02" + low
+    data = rng.integers(0, 256, nbytes, dtype=np.uint8)
+    d = torch.from_numpy(data).cuda()
+    for first in (3, (1 << 64) - 100000):
+        out = sf.encrypt_private(key, ctr0, d, first_block=first)
+        # the oracle takes the blocks of a sum beyond 2^64 from 0 on
+        split = min(nbytes, 16 * ((1 << 64) - first))
+        ref = oracle.ctr_xor(key, ctr0, data[:split], first_block=first)
+        if split < nbytes:
+            ref = np.concatenate([ref, oracle.ctr_xor(key, ctr0, data[split:], first_block=0)])
+        assert np.array_equal(out.cpu().numpy(), ref)
+    sf.encrypt_private(key, ctr0, out, out=out, first_block=first)  # in place, decrypt
+    assert np.array_equal(out.cpu().numpy(), data)
+
+
 def test_published_ctr_vector_on_gpu():
     from conftest import golden
     rows = golden("sp800_38a_ctr_aes128.txt")
