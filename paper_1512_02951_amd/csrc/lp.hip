@@ -171,6 +171,17 @@ __device__ __forceinline__ void split_int(int32_t q, uint32_t &hi, uint32_t &lo)
   }
 }
 
+// Puts the operand pair of a private integer in half e of the words hi and lo
+// of the lanes whose position it is.
+template <bool BF, int e>
+__device__ __forceinline__ void merge_private(bool mine, int32_t q, uint32_t &hi, uint32_t &lo) {
+  uint32_t qh, ql;
+  split_int<BF>(q, qh, ql);
+  const uint32_t put = e ? ((hi & 0x0000ffffu) | (qh << 16)) : ((hi & 0xffff0000u) | qh);
+  hi = mine ? put : hi;
+  if constexpr (BF) lo |= mine ? ql << (16 * e) : 0u;
+}
+
 // Four pixel bytes (one row word) -> four exact 16-bit operand values in two
 // words.  fp16: 0x6400 | x is 1024 + x, so one byte permute and one packed
 // subtraction of 1024 give x.  bf16: the high half of the FP32 value.
@@ -283,24 +294,17 @@ __device__ __forceinline__ q2v4 lp_quant(const q2v4 &a, const LpQ2 &Q) {
   return c;
 }
 
-// Coefficient bookkeeping of zigzag position z: compile-time for "DC + k AC"
-// selections, wave-uniform otherwise.  rank = rank among the private
-// (private) or the public positions.
+// Coefficient bookkeeping of zigzag position z of a "DC + k AC" selection:
+// rank among the private (private) or the public positions.
 struct ZSlot {
   uint32_t priv;
   uint32_t rank;
 };
 template <class MP>
-__device__ __forceinline__ ZSlot zslot(uint64_t mask, int z) {
+__device__ __forceinline__ ZSlot zslot(int z) {
   ZSlot c;
-  if constexpr (MP::kStatic) {
-    c.priv = z < MP::kNPriv ? 1u : 0u;
-    c.rank = c.priv ? (uint32_t)z : (uint32_t)(z - MP::kNPriv);
-  } else {
-    const uint32_t before = (uint32_t)__builtin_popcountll(mask & ((1ull << z) - 1ull));
-    c.priv = (uint32_t)((mask >> z) & 1u);
-    c.rank = c.priv ? before : (uint32_t)z - before;
-  }
+  c.priv = z < MP::kNPriv ? 1u : 0u;
+  c.rank = c.priv ? (uint32_t)z : (uint32_t)(z - MP::kNPriv);
   return c;
 }
 
@@ -488,25 +492,20 @@ __device__ __forceinline__ uint32_t apply_codes(uint32_t rec, uint32_t m) {
   return rec + (m & ~m1 & 0x01010101u) - (m & m1 & 0x01010101u);
 }
 
-template <class MP>
-__device__ __forceinline__ uint64_t mask_of(const TileGeom &g) {
-  return MP::kStatic ? g.mask : opaque_u64(g.mask);
-}
-
 // The lane's coefficient of the slot pair at zigzag positions z0 (lane half
 // 0) and z0 + 4 (lane half 1), with the stage and fragment offsets of its
-// value.  Private integers sit in the stage as int16 [rank][64 blocks];
-// public values of a half in the public stage as [rank][32 blocks].  For
-// "DC + k AC" selections two private (or two public) positions of a pair
-// are 4 ranks apart, so the offsets are a per-lane base plus a constant.
+// value, for "DC + k AC" selections.  Private integers sit in the stage as
+// int16 [rank][64 blocks]; public values of a half in the public stage as
+// [rank][32 blocks].  Two private (or two public) positions of a pair are 4
+// ranks apart, so the offsets are a per-lane base plus a constant.
 template <class MP>
 struct Pair {
   ZSlot c0, c1;
   bool any_priv, both_priv, any_pub, both_pub;
   bool mine_priv;
-  __device__ __forceinline__ Pair(uint64_t mask, int z0, uint32_t h) {
-    c0 = zslot<MP>(mask, z0);
-    c1 = zslot<MP>(mask, z0 + 4);
+  __device__ __forceinline__ Pair(int z0, uint32_t h) {
+    c0 = zslot<MP>(z0);
+    c1 = zslot<MP>(z0 + 4);
     any_priv = (c0.priv | c1.priv) != 0u;
     both_priv = (c0.priv & c1.priv) != 0u;
     any_pub = !both_priv;
@@ -516,19 +515,46 @@ struct Pair {
   // stage byte offset of the private integer this lane reads (for a pair with
   // one private half, that half's integer, read by every lane)
   __device__ __forceinline__ uint32_t priv_off(uint32_t jb, uint32_t h) const {
-    if constexpr (MP::kStatic) {
-      return both_priv ? 128u * c0.rank + (2u * jb + 512u * h) : 128u * (c0.priv ? c0.rank : c1.rank) + 2u * jb;
-    } else {
-      const uint32_t r = both_priv ? (h ? c1.rank : c0.rank) : (c0.priv ? c0.rank : c1.rank);
-      return 128u * r + 2u * jb;
-    }
-  }
-  // public rank this lane stores or loads (for a pair with one public half,
-  // that half's rank)
-  __device__ __forceinline__ uint32_t pub_rank(uint32_t h) const {
-    return both_pub ? (h ? c1.rank : c0.rank) : (c0.priv ? c1.rank : c0.rank);
+    return both_priv ? 128u * c0.rank + (2u * jb + 512u * h) : 128u * (c0.priv ? c0.rank : c1.rank) + 2u * jb;
   }
 };
+
+// Selections known only at run time.  Branches and rank arithmetic per
+// position (64 of each) cost these kernels their registers: 2.4 times the
+// compiled selections' time, with 88-272 bytes of scratch.  Here the positions
+// are taken in the order of a lane's operand slots (slot 4 (z / 8) + z % 4
+// of lane half (z / 4) % 2): the ranks of both halves' 32 slots are bytes in LDS
+// (RankTable, written once per workgroup), a public value's address is one
+// multiply-add on its byte, and only slots that hold a private position in
+// either half are branched on, by a bit of `any`.
+// Measured on 8192^2 with six private positions that are no prefix: fp16 frag
+// 172 -> 72 us, defrag 147 -> 51; bf16 171 -> 79 and 147 -> 53 (DC + 9 AC,
+// compiled: 75 / 56 and 79 / 59).
+struct RankTable {
+  uint4 rank[2][2];  // [lane half]: 32 bytes, the rank of the slot's position among its kind
+};
+
+template <class MP>
+constexpr uint32_t kRankBytes = MP::kStatic ? 0u : (uint32_t)sizeof(RankTable);
+
+struct RunSel {
+  uint32_t any;   // bit slot: the position of either lane half is private (wave-uniform)
+  uint32_t mine;  // bit slot: this lane's position is private
+};
+
+// Called by the whole wave; wave 0 also fills the table.
+__device__ __forceinline__ RunSel run_sel(uint64_t mask, int lane, bool fill, RankTable &T) {
+  const uint32_t slot = (uint32_t)lane & 31u, h = (uint32_t)lane >> 5;
+  const uint32_t z = 8u * (slot >> 2) + (slot & 3u) + 4u * h;
+  const uint32_t before = (uint32_t)__builtin_popcountll(mask & ((1ull << z) - 1ull));
+  const bool priv = (mask >> z) & 1u;
+  if (fill) reinterpret_cast<uint8_t *>(T.rank)[lane] = (uint8_t)(priv ? before : z - before);
+  const uint64_t bits = __builtin_amdgcn_ballot_w64(priv);
+  RunSel s;
+  s.any = (uint32_t)bits | (uint32_t)(bits >> 32);
+  s.mine = h ? (uint32_t)(bits >> 32) : (uint32_t)bits;
+  return s;
+}
 
 // Moves the private integers of a partial tile (ntb < 64 blocks) between
 // the stage layout [rank][64] and the fragment's [rank][ntb] (pack: before
@@ -567,7 +593,10 @@ __global__ __launch_bounds__(512, lp_waves_per_eu<BF>()) void lp_frag_kernel(LpA
   const uint32_t nw = blockDim.x >> 6;
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const TileGeom &g = a.g;
-  LpQ2 *s_q2 = reinterpret_cast<LpQ2 *>(s_dyn);
+  RankTable *s_rank = reinterpret_cast<RankTable *>(s_dyn);
+  RunSel rs{0u, 0u};
+  if constexpr (!MP::kStatic) rs = run_sel(g.mask, lane, wave == 0u, s_rank[0]);
+  LpQ2 *s_q2 = reinterpret_cast<LpQ2 *>(s_dyn + kRankBytes<MP>);
   if (a.aes.enabled) aes_load_tables(s_aes, a.aes_t0, a.aes.key, threadIdx.x, blockDim.x);
   load_lp_tables<BF>(s_tab, a.tables, threadIdx.x, blockDim.x);
   for (uint32_t i = threadIdx.x; i < 64u * a.npass; i += blockDim.x) {
@@ -577,9 +606,8 @@ __global__ __launch_bounds__(512, lp_waves_per_eu<BF>()) void lp_frag_kernel(LpA
   }
   __syncthreads();
   WaveLds W;
-  W.priv = s_dyn + 64u * a.npass * sizeof(LpQ2) + wave * a.wave_lds;
+  W.priv = s_dyn + kRankBytes<MP> + 64u * a.npass * sizeof(LpQ2) + wave * a.wave_lds;
   W.pub = W.priv + kFragGroup * a.pstride;
-  const uint64_t mask = mask_of<MP>(g);
   const uint32_t h = (uint32_t)lane >> 5, jl = (uint32_t)lane & 31u;
   const uint32_t stride = gridDim.x * nw;
   const uint32_t npriv = g.npriv, npub = g.npub;
@@ -663,6 +691,36 @@ __global__ __launch_bounds__(512, lp_waves_per_eu<BF>()) void lp_frag_kernel(LpA
         // inverse operands; private ones are the integers
         uint4 chi[4], clo[4];
         bool has_lo[4];
+        if constexpr (!MP::kStatic) {
+          const RankTable *rt = s_rank + opaque_zero();  // read per half: not 32 ranks held by the lane
+          const uint4 rk[2] = {rt->rank[h][0], rt->rank[h][1]};
+          const uint32_t *rw = reinterpret_cast<const uint32_t *>(rk);
+          static_for<0, 4>([&](auto sc) {
+            constexpr int s = decltype(sc)::value;
+            uint32_t hw[4], lw[4];
+            static_for<0, 4>([&](auto pc) {
+              constexpr int pr = decltype(pc)::value, slot0 = 8 * s + 2 * pr;
+              hw[pr] = pack16<BF>(acc[s / 2][slot0 % 16], acc[s / 2][slot0 % 16 + 1]);
+              lw[pr] = 0u;
+              static_for<0, 2>([&](auto ec) {
+                constexpr int e = decltype(ec)::value, slot = slot0 + e;
+                const uint32_t row = (rw[slot / 4] >> (8 * (slot % 4))) & 0xffu;
+                const uint16_t v = (uint16_t)(hw[pr] >> (16 * e));
+                if ((rs.any >> slot) & 1u) {
+                  const bool mine = (rs.mine >> slot) & 1u;
+                  const int32_t q = (int32_t) * reinterpret_cast<const int16_t *>(stage + 128u * (mine ? row : 0u) + 2u * jb);
+                  merge_private<BF, e>(mine, q, hw[pr], lw[pr]);
+                  if (!mine) *reinterpret_cast<uint16_t *>(W.pub + 64u * row + 2u * jl) = v;
+                } else {
+                  *reinterpret_cast<uint16_t *>(W.pub + 64u * row + 2u * jl) = v;
+                }
+              });
+            });
+            chi[s] = make_uint4(hw[0], hw[1], hw[2], hw[3]);
+            clo[s] = make_uint4(lw[0], lw[1], lw[2], lw[3]);
+            has_lo[s] = BF && ((rs.any >> (8 * s)) & 0xffu) != 0u;
+          });
+        } else
         static_for<0, 4>([&](auto sc) {
           constexpr int s = decltype(sc)::value, mt = s / 2, sg = s % 2;
           uint32_t hw[4], lw[4];
@@ -674,7 +732,7 @@ __global__ __launch_bounds__(512, lp_waves_per_eu<BF>()) void lp_frag_kernel(LpA
             uint32_t lo = 0u;
             static_for<0, 2>([&](auto ec) {
               constexpr int e = decltype(ec)::value, r = r0 + e;
-              const Pair<MP> P(mask, 32 * mt + 8 * (r / 4) + (r % 4), h);
+              const Pair<MP> P(32 * mt + 8 * (r / 4) + (r % 4), h);
               if (P.any_priv) {
                 const int32_t q = (int32_t) * reinterpret_cast<const int16_t *>(stage + P.priv_off(jb, h));
                 uint32_t qh, ql;
@@ -687,11 +745,8 @@ __global__ __launch_bounds__(512, lp_waves_per_eu<BF>()) void lp_frag_kernel(LpA
               }
               if (P.any_pub && !P.mine_priv) {
                 const uint16_t v = bv ? (uint16_t)(e ? (w >> 16) : w) : (uint16_t)0;
-                if constexpr (MP::kStatic)
-                  *reinterpret_cast<uint16_t *>(W.pub + (P.both_pub ? 64u * P.c0.rank + (2u * jl + 256u * h)
-                                                                    : 64u * P.c1.rank + 2u * jl)) = v;
-                else
-                  *reinterpret_cast<uint16_t *>(W.pub + 64u * P.pub_rank(h) + 2u * jl) = v;
+                *reinterpret_cast<uint16_t *>(W.pub + (P.both_pub ? 64u * P.c0.rank + (2u * jl + 256u * h)
+                                                                  : 64u * P.c1.rank + 2u * jl)) = v;
               }
             });
             hw[pr] = w;
@@ -801,13 +856,15 @@ __global__ __launch_bounds__(512, lp_waves_per_eu<BF>()) void lp_defrag_kernel(L
   const uint32_t nw = blockDim.x >> 6;
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const TileGeom &g = a.g;
+  RankTable *s_rank = reinterpret_cast<RankTable *>(s_dyn);
+  RunSel rs{0u, 0u};
+  if constexpr (!MP::kStatic) rs = run_sel(g.mask, lane, wave == 0u, s_rank[0]);
   if (a.aes.enabled) aes_load_tables(s_aes, a.aes_t0, a.aes.key, threadIdx.x, blockDim.x);
   load_lp_tables<BF>(s_tab, a.tables, threadIdx.x, blockDim.x);
   __syncthreads();
   WaveLds W;
-  W.priv = s_dyn + wave * a.wave_lds;
+  W.priv = s_dyn + kRankBytes<MP> + wave * a.wave_lds;
   W.pub = nullptr;
-  const uint64_t mask = mask_of<MP>(g);
   const uint32_t h = (uint32_t)lane >> 5, jl = (uint32_t)lane & 31u;
   const uint32_t stride = gridDim.x * nw;
   const uint32_t npub = g.npub;
@@ -850,6 +907,39 @@ __global__ __launch_bounds__(512, lp_waves_per_eu<BF>()) void lp_defrag_kernel(L
         const uint32_t vbase = 2u * (nt * npub * m0 + jl), vbase4 = vbase + 8u * mh * h;
         uint4 chi[4], clo[4];
         bool has_lo[4];
+        if constexpr (!MP::kStatic) {
+          const RankTable *rt = s_rank + opaque_zero();  // read per half: not 32 ranks held by the lane
+          const uint4 rk[2] = {rt->rank[h][0], rt->rank[h][1]};
+          const uint32_t *rw = reinterpret_cast<const uint32_t *>(rk);
+          uint32_t pv[32];
+          // private slots load some public value of the block, not used
+          static_for<0, 32>([&](auto rc) {
+            constexpr int slot = decltype(rc)::value;
+            const uint32_t row = (rw[slot / 4] >> (8 * (slot % 4))) & 0xffu;
+            pv[slot] = __builtin_amdgcn_raw_buffer_load_b16(prs, vbase + __umul24(row, 2u * mh), 0, 0);
+          });
+          static_for<0, 4>([&](auto sc) {
+            constexpr int s = decltype(sc)::value;
+            uint32_t hw[4], lw[4];
+            static_for<0, 4>([&](auto pc) {
+              constexpr int pr = decltype(pc)::value, slot0 = 8 * s + 2 * pr;
+              hw[pr] = pv[slot0] | (pv[slot0 + 1] << 16);
+              lw[pr] = 0u;
+              static_for<0, 2>([&](auto ec) {
+                constexpr int e = decltype(ec)::value, slot = slot0 + e;
+                if ((rs.any >> slot) & 1u) {
+                  const bool mine = (rs.mine >> slot) & 1u;
+                  const uint32_t row = (rw[slot / 4] >> (8 * (slot % 4))) & 0xffu;
+                  const int32_t q = (int32_t) * reinterpret_cast<const int16_t *>(stage + 128u * (mine ? row : 0u) + 2u * jb);
+                  merge_private<BF, e>(mine, q, hw[pr], lw[pr]);
+                }
+              });
+            });
+            chi[s] = make_uint4(hw[0], hw[1], hw[2], hw[3]);
+            clo[s] = make_uint4(lw[0], lw[1], lw[2], lw[3]);
+            has_lo[s] = BF && ((rs.any >> (8 * s)) & 0xffu) != 0u;
+          });
+        } else
         static_for<0, 4>([&](auto sc) {
           constexpr int s = decltype(sc)::value, mt = s / 2, sg = s % 2;
           uint32_t hw[4], lw[4];
@@ -860,7 +950,7 @@ __global__ __launch_bounds__(512, lp_waves_per_eu<BF>()) void lp_defrag_kernel(L
             uint32_t w = 0u, lo = 0u;
             static_for<0, 2>([&](auto ec) {
               constexpr int e = decltype(ec)::value, r = r0 + e;
-              const Pair<MP> P(mask, 32 * mt + 8 * (r / 4) + (r % 4), h);
+              const Pair<MP> P(32 * mt + 8 * (r / 4) + (r % 4), h);
               uint32_t v = 0u;
               if (P.any_priv) {
                 const int32_t q = (int32_t) * reinterpret_cast<const int16_t *>(stage + P.priv_off(jb, h));
@@ -873,12 +963,9 @@ __global__ __launch_bounds__(512, lp_waves_per_eu<BF>()) void lp_defrag_kernel(L
                 any_lo = true;
               }
               if (P.any_pub) {
-                uint32_t pv;
-                if constexpr (MP::kStatic)
-                  pv = P.both_pub ? __builtin_amdgcn_raw_buffer_load_b16(prs, vbase4, (int)(2u * mh * P.c0.rank), 0)
-                                  : __builtin_amdgcn_raw_buffer_load_b16(prs, vbase, (int)(2u * mh * P.c1.rank), 0);
-                else
-                  pv = __builtin_amdgcn_raw_buffer_load_b16(prs, vbase + 2u * mh * P.pub_rank(h), 0, 0);
+                const uint32_t pv = P.both_pub
+                                        ? __builtin_amdgcn_raw_buffer_load_b16(prs, vbase4, (int)(2u * mh * P.c0.rank), 0)
+                                        : __builtin_amdgcn_raw_buffer_load_b16(prs, vbase, (int)(2u * mh * P.c1.rank), 0);
                 if (!P.mine_priv) v = pv;
               }
               w |= v << (16 * e);
@@ -924,9 +1011,12 @@ __global__ __launch_bounds__(512, lp_waves_per_eu<BF>()) void lp_defrag_kernel(L
 
 // ---------------------------------------------------------------------------
 // launchers
-// Dynamic LDS of a workgroup: `shared` (frag: the quantiser's B operands)
-// plus `per_wave` for each wavefront (private stages; frag: also the public
+// Dynamic LDS of a workgroup: `shared` (the rank table of selections known at
+// run time; frag: the quantiser's B operands) plus `per_wave` for each wavefront (private stages; frag: also the public
 // stage of one half).
+bool compiled_selection(uint64_t mask) {
+  return mask == (1ull << 2) - 1 || mask == (1ull << 3) - 1 || mask == (1ull << 6) - 1 || mask == (1ull << 10) - 1;
+}
 struct LpLdsPlan {
   size_t fixed, shared, per_wave;
 };
@@ -934,7 +1024,7 @@ LpLdsPlan lp_lds_plan(const Geom &g, int which) {
   const uint32_t npass = (g.npriv + 15u) / 16u, pstride = (2u * g.npriv * 64u + 15u) & ~15u;
   LpLdsPlan p;
   p.fixed = sizeof(AesLds) + (g.precision == SF_BF16 ? sizeof(LpLds<true>) : sizeof(LpLds<false>));
-  p.shared = which == 0 ? 64u * npass * sizeof(LpQ2) : 0u;
+  p.shared = (compiled_selection(g.mask) ? 0u : sizeof(RankTable)) + (which == 0 ? 64u * npass * sizeof(LpQ2) : 0u);
   p.per_wave = (size_t)(which == 0 ? kFragGroup : kDefragGroup) * pstride + (which == 0 ? (size_t)64u * g.npub : 0u);
   return p;
 }

@@ -165,6 +165,15 @@ def test_lp_runtime_masks_and_clear_private(prec, mask):
     _check(x, mask, prec, None, None, "lp runtime mask")
 
 
+@pytest.mark.parametrize("prec", ["fp16", "bf16"])
+@pytest.mark.parametrize("mask", [0x9F, 0x7FFF, 0x0F0F0F0F, 0xF0F0F0F0F0F0F0F0, 0x8000000000000000, 1, (1 << 64) - 2])
+def test_lp_runtime_masks_by_operand_slot(prec, mask):
+    # private positions in one lane half's slots, in both, in every K-step, in
+    # the first and the last slot alone, and all but one; a partial last half
+    x = synth.image(72, 136, 1, 3, 5).numpy()
+    _check(x, mask, prec, synth.aes_key(3), synth.ctr0(3, 5), "lp slots")
+
+
 # An 8x8 block whose bf16 public part (DC public, zigzag positions 1-5
 # private) reconstructs about 1.7 away from some of its samples: found by a
 # search over saturated blocks maximising max |IDCT(stored) - x| with bf16
