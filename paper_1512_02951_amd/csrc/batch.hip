@@ -262,7 +262,9 @@ __global__ __launch_bounds__(kThreads, 3) void defrag_batch_kernel(BatchArgs a) 
     in.exc = d.exc;
     const TileLane L = tile_lane(d.g, t, lane);
     dispatch_mask<kAny>(d.g.mask, [&](auto mp) __attribute__((always_inline)) {
-      defrag_tile<decltype(mp)>(d.g, in, t, L, lane, lp, s_aes, enc, d.ctr_hi, d.ctr_lo, a.K);
+      float c[64];
+      defrag_load_public<decltype(mp)>(d.g, in, L, lane, c);
+      defrag_tile<decltype(mp)>(d.g, in, t, L, lane, lp, s_aes, enc, d.ctr_hi, d.ctr_lo, a.K, c);
     });
   });
 }

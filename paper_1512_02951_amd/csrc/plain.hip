@@ -32,16 +32,12 @@ struct DefragKernelArgs {
 };
 
 // Tuning knobs (compile-time): minimum waves per SIMD requested from the
-// register allocator, and whether frag loads the next tile's pixels before
-// working on the current one.
+// register allocator.
 #ifndef SF_FRAG_WAVES_PER_EU
 #define SF_FRAG_WAVES_PER_EU 3
 #endif
 #ifndef SF_DEFRAG_WAVES_PER_EU
 #define SF_DEFRAG_WAVES_PER_EU 3
-#endif
-#ifndef SF_FRAG_PREFETCH
-#define SF_FRAG_PREFETCH 0
 #endif
 
 // Each wave walks tiles t, t + stride, ... (kLoop, the resident grids), or
@@ -58,56 +54,39 @@ __global__ __launch_bounds__(kMaxThreads, SF_FRAG_WAVES_PER_EU) void frag_fp32_k
   const int lane = threadIdx.x & 63;
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const uint32_t nw = blockDim.x >> 6;
-  if (a.aes.enabled) aes_load_tables(s_aes, a.aes_t0, a.aes.key, threadIdx.x, blockDim.x);
-  if constexpr (kQ2Mfma)
-    if (threadIdx.x < 64) s_q2[lane] = q2_operands(a.o.q2, private_ac<MP>(a.g.mask, lane & 15), lane);
-  __syncthreads();
   constexpr uint32_t kStage = kQ2Mfma ? kQ2StageBytes : 0u;
   uint8_t *lp = s_dyn + wave * (a.lds_priv_bytes + kStage);
   uint8_t *q2stage = lp + a.lds_priv_bytes;
   const Q2Operands *Q = &s_q2[kQ2Mfma ? lane : 0];
   const uint32_t stride = gridDim.x * nw;
   uint32_t t = blockIdx.x * nw + wave;
-  if (t >= a.g.ntiles) return;
-  if constexpr (!kLoop) {
-    const TileLane L = tile_lane(a.g, t, lane);
-    uint32_t xs[16];
-    load_block(a.g, L, xs);
-    if constexpr (kQ2Mfma)
-      frag_tile<MP, true>(a.g, a.o, t, L, xs, lane, lp, s_aes, a.aes.enabled, a.aes.ctr_hi, a.aes.ctr_lo, a.K,
-                          q2stage, Q);
-    else
-      frag_tile<MP, false>(a.g, a.o, t, L, xs, lane, lp, s_aes, a.aes.enabled, a.aes.ctr_hi, a.aes.ctr_lo, a.K);
-    return;
-  }
-#if SF_FRAG_PREFETCH
-  TileLane L = tile_lane(a.g, t, lane);
+  // the tables' loads, then the first tile's pixels, then the waits for the
+  // tables only: the pixels arrive while LDS is filled.  A workgroup used to
+  // wait for its tables, then for its pixels (round trips: 1080 x 1920 RGB,
+  // DC + 5 AC 20.7 -> 20.0 us; 4096^2 RGB 83.3 -> 81.2).
+  AesFill fill;
+  Q2Operands q2op;
+  const int first = threadIdx.x < 64 ? private_ac<MP>(a.g.mask, lane & 15) : -1;
+  fill.load(a.aes_t0, a.aes.key, threadIdx.x);
+  if constexpr (kQ2Mfma) q2op = q2_operands(a.o.q2, first, lane);
+  TileLane L = tile_lane(a.g, min(t, a.g.ntiles - 1u), lane);
   uint32_t xs[16];
   load_block(a.g, L, xs);
-  for (;;) {
-    const uint32_t tn = t + stride;
-    const bool more = tn < a.g.ntiles;
-    TileLane Ln = L;
-    uint32_t xn[16];
-    if (more) {
-      Ln = tile_lane(a.g, tn, lane);
-      load_block(a.g, Ln, xn);
-    }
+  __builtin_amdgcn_sched_barrier(0);
+  if (wave == 0u) {
+    fill.store(s_aes, threadIdx.x);
+    if constexpr (kQ2Mfma) s_q2[lane] = q2op;
+  }
+  __syncthreads();
+  if (t >= a.g.ntiles) return;
+  if constexpr (!kLoop) {
     frag_tile<MP, kQ2Mfma>(a.g, a.o, t, L, xs, lane, lp, s_aes, a.aes.enabled, a.aes.ctr_hi, a.aes.ctr_lo, a.K,
                            q2stage, Q);
-    if (!more) break;
-    t = tn;
-    L = Ln;
-#pragma unroll
-    for (int w = 0; w < 16; ++w) xs[w] = xn[w];
+    return;
   }
-#else
   if constexpr (kQ2Mfma) {
     // the next tile's pixels are loaded from inside frag_tile, once the
     // current ones have been consumed
-    TileLane L = tile_lane(a.g, t, lane);
-    uint32_t xs[16];
-    load_block(a.g, L, xs);
     for (;;) {
       const uint32_t tn = t + stride;
       const bool more = tn < a.g.ntiles;
@@ -121,14 +100,14 @@ __global__ __launch_bounds__(kMaxThreads, SF_FRAG_WAVES_PER_EU) void frag_fp32_k
       L = Ln;
     }
   } else {
-    for (; t < a.g.ntiles; t += stride) {
-      const TileLane L = tile_lane(a.g, t, lane);
-      uint32_t xs[16];
-      load_block(a.g, L, xs);
+    for (;;) {
       frag_tile<MP, false>(a.g, a.o, t, L, xs, lane, lp, s_aes, a.aes.enabled, a.aes.ctr_hi, a.aes.ctr_lo, a.K);
+      t += stride;
+      if (t >= a.g.ntiles) break;
+      L = tile_lane(a.g, t, lane);
+      load_block(a.g, L, xs);
     }
   }
-#endif
 }
 
 template <class MP>
@@ -138,13 +117,27 @@ __global__ __launch_bounds__(kMaxThreads, SF_DEFRAG_WAVES_PER_EU) void defrag_fp
   const int lane = threadIdx.x & 63;
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const uint32_t nw = blockDim.x >> 6;
-  if (a.aes.enabled) aes_load_tables(s_aes, a.aes_t0, a.aes.key, threadIdx.x, blockDim.x);
-  __syncthreads();
   uint8_t *lp = s_dyn + wave * a.lds_priv_bytes;
   const uint32_t stride = gridDim.x * nw;
-  for (uint32_t t = blockIdx.x * nw + wave; t < a.g.ntiles; t += stride)
-    defrag_tile<MP>(a.g, a.in, t, tile_lane(a.g, t, lane), lane, lp, s_aes, a.aes.enabled, a.aes.ctr_hi,
-                    a.aes.ctr_lo, a.K);
+  uint32_t t = blockIdx.x * nw + wave;
+  // as in frag: the first tile's public values are in flight while the tables
+  // arrive and LDS is filled
+  AesFill fill;
+  fill.load(a.aes_t0, a.aes.key, threadIdx.x);
+  TileLane L = tile_lane(a.g, min(t, a.g.ntiles - 1u), lane);
+  float c[64];
+  defrag_load_public<MP>(a.g, a.in, L, lane, c);
+  __builtin_amdgcn_sched_barrier(0);
+  if (wave == 0u) fill.store(s_aes, threadIdx.x);
+  __syncthreads();
+  if (t >= a.g.ntiles) return;
+  for (;;) {
+    defrag_tile<MP>(a.g, a.in, t, L, lane, lp, s_aes, a.aes.enabled, a.aes.ctr_hi, a.aes.ctr_lo, a.K, c);
+    t += stride;
+    if (t >= a.g.ntiles) break;
+    L = tile_lane(a.g, t, lane);
+    defrag_load_public<MP>(a.g, a.in, L, lane, c);
+  }
 }
 
 uint32_t lds_priv_bytes(const Geom &g) { return (2u * g.npriv * 64u + 15u) & ~15u; }

@@ -234,14 +234,19 @@ __device__ __forceinline__ int private_ac(uint64_t mask, int a) {
   return n;
 }
 
+// Straight-line (see AesFill): columns without a coefficient load row 0.
 __device__ __forceinline__ Q2Operands q2_operands(const uint32_t *q2, int n, int lane) {
   Q2Operands o;
-  const int g = lane >> 4;
+  static_assert(kQ2RowWords % 4 == 0, "rows of whole 16-byte words");
+  const uint32_t *row = q2 + (n >= 0 ? n * kQ2RowWords : 0);
 #pragma unroll
-  for (int L = 0; L < 3; ++L)
+  for (int L = 0; L < 3; ++L) {
+    const q2v4 v = *reinterpret_cast<const q2v4 *>(row + 16 * L + 4 * (lane >> 4));
 #pragma unroll
-    for (int j = 0; j < 4; ++j) o.b[L][j] = n >= 0 ? (int)q2[n * kQ2RowWords + 16 * L + 4 * g + j] : 0;
-  o.bias = n >= 0 ? q2[n * kQ2RowWords + 48] : 0u;
+    for (int j = 0; j < 4; ++j) o.b[L][j] = n >= 0 ? v[j] : 0;
+  }
+  const uint32_t bias = row[48];
+  o.bias = n >= 0 ? bias : 0u;
   return o;
 }
 
@@ -403,19 +408,15 @@ __device__ __forceinline__ TileLane tile_lane(const TileGeom &g, uint32_t t, int
   return L;
 }
 
-// The lane's 8x8 block as 16 words (row r = words 2r, 2r+1), zero if no block.
+// The lane's 8x8 block as 16 words (row r = words 2r, 2r+1).  Lanes without a
+// block read the image's first one (org 0): nothing of theirs is stored.
 __device__ __forceinline__ void load_block(const TileGeom &g, const TileLane &L, uint32_t (&xs)[16]) {
-  if (L.valid) {
-    const uint8_t *p = g.pix + L.org;
+  const uint8_t *p = g.pix + L.org;
 #pragma unroll
-    for (int r = 0; r < 8; ++r) {
-      const uint2 v = *reinterpret_cast<const uint2 *>(p + (size_t)r * g.W);
-      xs[2 * r] = v.x;
-      xs[2 * r + 1] = v.y;
-    }
-  } else {
-#pragma unroll
-    for (int w = 0; w < 16; ++w) xs[w] = 0u;
+  for (int r = 0; r < 8; ++r) {
+    const uint2 v = *reinterpret_cast<const uint2 *>(p + (size_t)r * g.W);
+    xs[2 * r] = v.x;
+    xs[2 * r + 1] = v.y;
   }
 }
 
@@ -639,18 +640,14 @@ __device__ __forceinline__ void frag_tile(const TileGeom &g, const FragOut &o, u
   wave_lds_sync();
 }
 
+// The lane's public values into c (natural order; private positions untouched).
 template <class MP>
-__device__ __forceinline__ void defrag_tile(const TileGeom &g, const DefragIn &in, uint32_t t, const TileLane &L,
-                                            int lane, uint8_t *lp, const AesLds &s_aes, uint32_t enc, uint64_t ctr_hi,
-                                            uint64_t ctr_lo, const DctK &K) {
+__device__ __forceinline__ void defrag_load_public(const TileGeom &g, const DefragIn &in, const TileLane &L, int lane,
+                                                   float (&c)[64]) {
   const uint64_t b0 = L.b0;
   const uint32_t nt = L.nt;
   const bool valid = L.valid != 0u;
   const uint64_t mask = MP::kStatic ? g.mask : opaque_u64(g.mask);
-
-  // public values first: their loads stay in flight while the private bytes
-  // are decrypted
-  float c[64];
   const __amdgpu_buffer_rsrc_t pub_rs = buffer_rsrc(in.pub + b0 * g.npub, g.npub * nt * 4u);
   // lanes past the tile's last block read lane 0's values (in range); their
   // results are never stored
@@ -662,6 +659,18 @@ __device__ __forceinline__ void defrag_tile(const TileGeom &g, const DefragIn &i
         c[n] = __uint_as_float(
             __builtin_amdgcn_raw_buffer_load_b32(pub_rs, pub_voff, (int)(pu * nt * 4u), kNonTemporal));
       });
+}
+
+// The rest of a tile, its public values in c: their loads stay in flight while
+// the private bytes are decrypted.
+template <class MP>
+__device__ __forceinline__ void defrag_tile(const TileGeom &g, const DefragIn &in, uint32_t t, const TileLane &L,
+                                            int lane, uint8_t *lp, const AesLds &s_aes, uint32_t enc, uint64_t ctr_hi,
+                                            uint64_t ctr_lo, const DctK &K, float (&c)[64]) {
+  const uint64_t b0 = L.b0;
+  const uint32_t nt = L.nt;
+  const bool valid = L.valid != 0u;
+  const uint64_t mask = MP::kStatic ? g.mask : opaque_u64(g.mask);
   tile_ctr_load(lp, in.priv + b0 * g.npriv * 2u, 2u * g.npriv * nt, lane, s_aes, enc, ctr_hi, ctr_lo,
                 b0 * g.npriv / 8u);
   wave_lds_sync();

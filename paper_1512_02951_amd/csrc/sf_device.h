@@ -184,7 +184,7 @@ struct AesKey {
 
 // Round tables and the expanded key, copied into LDS once per workgroup
 // (the key is read with wave-uniform broadcasts).
-struct AesLds {
+struct __attribute__((aligned(16))) AesLds {
   uint32_t t[4][256];
   uint32_t rk[44];
 };
@@ -200,6 +200,33 @@ __device__ __forceinline__ void aes_load_tables(AesLds &L, const uint32_t *__res
   }
   for (int i = tid; i < 44; i += nthreads) L.rk[i] = K.rk[i];
 }
+
+// The same in two steps, so that a kernel can issue the loads of its first
+// tile between them: load() starts the table and key loads, store() (by the
+// first wave) waits for those only and fills LDS while the tile's loads, issued
+// later, are in flight.  For the wait to be that exact, everything from load()
+// to store() is straight-line code: lanes without work load some valid address
+// instead of being branched round.
+struct AesFill {
+  uint4 v;
+  uint32_t rk;
+  __device__ __forceinline__ void load(const uint32_t *T0, const AesKey &K, uint32_t tid) {
+    v = reinterpret_cast<const uint4 *>(T0)[min(tid, 63u)];
+    rk = K.rk[min(tid, 43u)];
+  }
+  __device__ __forceinline__ static uint4 rot(const uint4 &w, uint32_t n) {  // left by n bits
+    return make_uint4((w.x << n) | (w.x >> (32u - n)), (w.y << n) | (w.y >> (32u - n)),
+                      (w.z << n) | (w.z >> (32u - n)), (w.w << n) | (w.w >> (32u - n)));
+  }
+  __device__ __forceinline__ void store(AesLds &L, uint32_t tid) const {
+    uint4 *t = reinterpret_cast<uint4 *>(L.t);
+    t[tid] = v;
+    t[64 + tid] = rot(v, 8);
+    t[128 + tid] = rot(v, 16);
+    t[192 + tid] = rot(v, 24);
+    if (tid < 44u) L.rk[tid] = rk;
+  }
+};
 
 // The lane index from an opaque instruction pair: values derived from it are
 // computed where they are used rather than held (or spilled) across a whole
