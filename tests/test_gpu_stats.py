@@ -112,6 +112,22 @@ def test_full_size_4096_rgb_strong_public():
     assert abs(got["block_entropy_y"][0] - ost.expected_block_entropy_uniform()) < 0.01
 
 
+@pytest.mark.parametrize("shape", [(1, 1024, 1024), (1, 4008, 4000)])
+@pytest.mark.parametrize("values", [1, 2, 40, 256])
+def test_joint_counts_above_a_byte_and_between_parts(shape, values):
+    # few bins: counts beyond 255 and beyond the 16-bit counters' spill limit,
+    # in workgroups that take one part of samples and in ones that take several
+    g = torch.Generator().manual_seed(values)
+    pick = torch.randperm(256, generator=g)[:values].to(torch.uint8)
+    x, y = (pick[torch.randint(0, values, shape, generator=g)].contiguous() for _ in range(2))
+    r = stats.StatsRunner("cuda")
+    r.launch(x.cuda(), y.cuda())
+    ref = torch.bincount(256 * x.flatten().long() + y.flatten().long(), minlength=65536).view(256, 256)
+    assert torch.equal(r.joint_histogram().cpu().long(), ref)
+    got = r.result()
+    assert got["hist_x"] == ref.sum(1).tolist() and got["hist_y"] == ref.sum(0).tolist()
+
+
 def test_tall_narrow_image_sums_stay_exact():
     # W = 8: one lane pair per band, 2^24 bands (4096 per wave): far more than
     # a 32-bit lane sum of squares could hold without the periodic flush.
