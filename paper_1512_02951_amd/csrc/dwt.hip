@@ -100,15 +100,20 @@ __global__ __launch_bounds__(kThreads) void dwt_frag_kernel(DwtArgs a) {
   __shared__ __attribute__((aligned(16))) uint8_t s_priv[kWaves][2 * kDwtPriv * 64];
   const int lane = threadIdx.x & 63;
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  if (a.aes.enabled) aes_load_tables(s_aes, a.aes_t0, a.aes.key, threadIdx.x, kThreads);
-  __syncthreads();
   uint8_t *lp = s_priv[wave];
   const TileGeom &g = a.g;
-  for (uint32_t t = blockIdx.x * kWaves + wave; t < g.ntiles; t += gridDim.x * kWaves) {
-    const TileLane L = tile_lane(g, t, lane);
+  // the first tile's pixels are in flight while the tables arrive (see AesFill)
+  uint32_t t = blockIdx.x * kWaves + wave;
+  AesFill fill;
+  fill.load(a.aes_t0, a.aes.key, threadIdx.x);
+  TileLane L = tile_lane(g, min(t, g.ntiles - 1u), lane);
+  uint32_t xs[16];
+  load_block(g, L, xs);
+  __builtin_amdgcn_sched_barrier(0);
+  if (wave == 0u) fill.store(s_aes, threadIdx.x);
+  __syncthreads();
+  while (t < g.ntiles) {
     const bool valid = L.valid != 0u;
-    uint32_t xs[16];
-    load_block(g, L, xs);
     int32_t c[64];
     static_for<0, 64>([&](auto pc) {
       constexpr int p = decltype(pc)::value;
@@ -132,7 +137,24 @@ __global__ __launch_bounds__(kThreads) void dwt_frag_kernel(DwtArgs a) {
     tile_ctr_store(lp, a.priv + L.b0 * kDwtPriv * 2u, 2u * kDwtPriv * nt, lane, s_aes, a.aes.enabled, a.aes.ctr_hi,
                    a.aes.ctr_lo, L.b0 * kDwtPriv / 8u);
     wave_lds_sync();
+    t += gridDim.x * kWaves;
+    if (t < g.ntiles) {
+      L = tile_lane(g, t, lane);
+      load_block(g, L, xs);
+    }
   }
+}
+
+// The lane's public values into c (positions of the private ones untouched).
+__device__ __forceinline__ void dwt_load_public(const DwtArgs &a, const TileLane &L, int lane, int32_t (&c)[64]) {
+  const __amdgpu_buffer_rsrc_t pub_rs = buffer_rsrc(a.pub + L.b0 * kDwtPub, kDwtPub * L.nt * 2u);
+  const int voff = L.valid ? lane * 2 : 0;  // lanes past the tile's end read lane 0's values, never stored
+  static_for<0, 64>([&](auto pc) {
+    constexpr int p = decltype(pc)::value;
+    constexpr int j = dwt_rank(p);
+    if constexpr (!dwt_private(p))
+      c[p] = (int32_t)(int16_t)__builtin_amdgcn_raw_buffer_load_b16(pub_rs, voff, (int)(j * L.nt * 2u), kNonTemporal);
+  });
 }
 
 __global__ __launch_bounds__(kThreads) void dwt_defrag_kernel(DwtArgs a) {
@@ -140,23 +162,20 @@ __global__ __launch_bounds__(kThreads) void dwt_defrag_kernel(DwtArgs a) {
   __shared__ __attribute__((aligned(16))) uint8_t s_priv[kWaves][2 * kDwtPriv * 64];
   const int lane = threadIdx.x & 63;
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  if (a.aes.enabled) aes_load_tables(s_aes, a.aes_t0, a.aes.key, threadIdx.x, kThreads);
-  __syncthreads();
   uint8_t *lp = s_priv[wave];
   const TileGeom &g = a.g;
-  for (uint32_t t = blockIdx.x * kWaves + wave; t < g.ntiles; t += gridDim.x * kWaves) {
-    const TileLane L = tile_lane(g, t, lane);
+  uint32_t t = blockIdx.x * kWaves + wave;
+  AesFill fill;
+  fill.load(a.aes_t0, a.aes.key, threadIdx.x);
+  TileLane L = tile_lane(g, min(t, g.ntiles - 1u), lane);
+  int32_t c[64];
+  dwt_load_public(a, L, lane, c);
+  __builtin_amdgcn_sched_barrier(0);
+  if (wave == 0u) fill.store(s_aes, threadIdx.x);
+  __syncthreads();
+  while (t < g.ntiles) {
     const bool valid = L.valid != 0u;
     const uint32_t nt = L.nt;
-    int32_t c[64];
-    const __amdgpu_buffer_rsrc_t pub_rs = buffer_rsrc(a.pub + L.b0 * kDwtPub, kDwtPub * nt * 2u);
-    const int voff = valid ? lane * 2 : 0;  // lanes past the tile's end read lane 0's values, never stored
-    static_for<0, 64>([&](auto pc) {
-      constexpr int p = decltype(pc)::value;
-      constexpr int j = dwt_rank(p);
-      if constexpr (!dwt_private(p))
-        c[p] = (int32_t)(int16_t)__builtin_amdgcn_raw_buffer_load_b16(pub_rs, voff, (int)(j * nt * 2u), kNonTemporal);
-    });
     tile_ctr_load(lp, a.priv + L.b0 * kDwtPriv * 2u, 2u * kDwtPriv * nt, lane, s_aes, a.aes.enabled, a.aes.ctr_hi,
                   a.aes.ctr_lo, L.b0 * kDwtPriv / 8u);
     wave_lds_sync();
@@ -178,6 +197,11 @@ __global__ __launch_bounds__(kThreads) void dwt_defrag_kernel(DwtArgs a) {
         for (int i = 0; i < 8; ++i) w[i >> 2] |= (uint32_t)((c[8 * r + i] + 128) & 0xff) << (8 * (i & 3));
         __builtin_nontemporal_store(((uint64_t)w[1] << 32) | w[0], reinterpret_cast<uint64_t *>(px + (size_t)r * g.W));
       }
+    }
+    t += gridDim.x * kWaves;
+    if (t < g.ntiles) {
+      L = tile_lane(g, t, lane);
+      dwt_load_public(a, L, lane, c);
     }
   }
 }

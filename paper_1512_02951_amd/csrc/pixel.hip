@@ -231,24 +231,33 @@ __global__ __launch_bounds__(kThreads) void pixel_frag_kernel(PixArgs a) {
   __shared__ Q2Operands s_q2[64];  // B operand per lane (same for every wave)
   const int lane = threadIdx.x & 63;
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  if (a.aes.enabled) aes_load_tables(s_aes, a.aes_t0, a.aes.key, threadIdx.x, kThreads);
-  if (threadIdx.x < 64) s_q2[lane] = q2_operands(a.q2, private_ac<MP>(a.g.mask, lane & 15), lane);
+  // the first tile's pixels are in flight while the tables arrive (see AesFill)
+  const TileGeom &g = a.g;
+  uint32_t t = blockIdx.x * kWaves + wave;
+  AesFill fill;
+  const int first = wave == 0u ? private_ac<MP>(g.mask, lane & 15) : -1;
+  fill.load(a.aes_t0, a.aes.key, threadIdx.x);
+  const Q2Operands q2op = q2_operands(a.q2, first, lane);
+  TileLane L = tile_lane(g, min(t, g.ntiles - 1u), lane);
+  uint32_t xs[16];
+  load_block(g, L, xs);
+  __builtin_amdgcn_sched_barrier(0);
+  if (wave == 0u) {
+    fill.store(s_aes, threadIdx.x);
+    s_q2[lane] = q2op;
+  }
   __syncthreads();
   uint8_t *lp = s_bits[wave];
   uint32_t *lw = reinterpret_cast<uint32_t *>(lp);
   uint8_t *stage = s_stage[wave];
-  const TileGeom &g = a.g;
   const uint32_t np = NP > 0 ? (uint32_t)NP : a.np;
   const uint32_t npair = (np + 1u) / 2u;
   const uint32_t dc = NP > 0 ? 1u : (uint32_t)(g.mask & 1u);
   constexpr int kNPair = NP > 0 ? (NP + 1) / 2 : 0;
-  for (uint32_t t = blockIdx.x * kWaves + wave; t < g.ntiles; t += gridDim.x * kWaves) {
-    const TileLane L = tile_lane(g, t, lane);
+  while (t < g.ntiles) {
     const bool valid = L.valid != 0u;
     const cu32_ptr inv = inv_table();
     for (uint32_t i = lane; i < kPixRegion / 16u; i += 64u) reinterpret_cast<uint4 *>(lp)[i] = make_uint4(0, 0, 0, 0);
-    uint32_t xs[16];
-    load_block(g, L, xs);
     uint32_t S = 0;
 #pragma unroll
     for (int w = 0; w < 16; ++w) S = __builtin_amdgcn_udot4(xs[w], 0x01010101u, S, false);
@@ -318,6 +327,22 @@ __global__ __launch_bounds__(kThreads) void pixel_frag_kernel(PixArgs a) {
     tile_ctr_store(lp, a.priv + (uint64_t)t * a.stride, tile_bytes(a, t), lane, s_aes, a.aes.enabled, a.aes.ctr_hi,
                    a.aes.ctr_lo, (uint64_t)t * (a.stride / 16u));
     wave_lds_sync();
+    t += gridDim.x * kWaves;
+    if (t < g.ntiles) {
+      L = tile_lane(g, t, lane);
+      load_block(g, L, xs);
+    }
+  }
+}
+
+// The lane's public rows (lanes without a block read the image's first).
+__device__ __forceinline__ void pixel_load_public(const PixArgs &a, const TileLane &L, uint32_t (&pw)[16]) {
+  const uint8_t *src = a.pub + L.org;
+#pragma unroll
+  for (int y = 0; y < 8; ++y) {
+    const uint64_t v = __builtin_nontemporal_load(reinterpret_cast<const uint64_t *>(src + (size_t)y * a.g.W));
+    pw[2 * y] = (uint32_t)v;
+    pw[2 * y + 1] = (uint32_t)(v >> 32);
   }
 }
 
@@ -327,32 +352,25 @@ __global__ __launch_bounds__(kThreads) void pixel_defrag_kernel(PixArgs a) {
   __shared__ __attribute__((aligned(16))) uint8_t s_bits[kWaves][kPixRegion];
   const int lane = threadIdx.x & 63;
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  if (a.aes.enabled) aes_load_tables(s_aes, a.aes_t0, a.aes.key, threadIdx.x, kThreads);
+  const TileGeom &g = a.g;
+  uint32_t t = blockIdx.x * kWaves + wave;
+  AesFill fill;
+  fill.load(a.aes_t0, a.aes.key, threadIdx.x);
+  TileLane L = tile_lane(g, min(t, g.ntiles - 1u), lane);
+  uint32_t pw[16];
+  pixel_load_public(a, L, pw);
+  __builtin_amdgcn_sched_barrier(0);
+  if (wave == 0u) fill.store(s_aes, threadIdx.x);
   __syncthreads();
   uint8_t *lp = s_bits[wave];
   const uint32_t *lw = reinterpret_cast<const uint32_t *>(lp);
-  const TileGeom &g = a.g;
   const uint32_t np = NP > 0 ? (uint32_t)NP : a.np;
   const uint32_t npair = (np + 1u) / 2u;
   const uint32_t dc = NP > 0 ? 1u : (uint32_t)(g.mask & 1u);
   constexpr int kNPair = NP > 0 ? (NP + 1) / 2 : 0;
-  for (uint32_t t = blockIdx.x * kWaves + wave; t < g.ntiles; t += gridDim.x * kWaves) {
-    const TileLane L = tile_lane(g, t, lane);
+  while (t < g.ntiles) {
     const bool valid = L.valid != 0u;
-    // public rows first: their loads are in flight during the decryption
-    uint32_t pw[16];
-    if (valid) {
-      const uint8_t *src = a.pub + L.org;
-#pragma unroll
-      for (int y = 0; y < 8; ++y) {
-        const uint64_t v = __builtin_nontemporal_load(reinterpret_cast<const uint64_t *>(src + (size_t)y * g.W));
-        pw[2 * y] = (uint32_t)v;
-        pw[2 * y + 1] = (uint32_t)(v >> 32);
-      }
-    } else {
-#pragma unroll
-      for (int w = 0; w < 16; ++w) pw[w] = 0u;
-    }
+    // the public rows are in flight during the decryption
     tile_ctr_load(lp, a.priv + (uint64_t)t * a.stride, tile_bytes(a, t), lane, s_aes, a.aes.enabled, a.aes.ctr_hi,
                   a.aes.ctr_lo, (uint64_t)t * (a.stride / 16u));
     wave_lds_sync();
@@ -395,6 +413,11 @@ __global__ __launch_bounds__(kThreads) void pixel_defrag_kernel(PixArgs a) {
         const uint32_t xlo = bytes_add(plo, rlo), xhi = bytes_add(phi, rhi);
         __builtin_nontemporal_store(((uint64_t)xhi << 32) | xlo, reinterpret_cast<uint64_t *>(dst + (size_t)y * g.W));
       }
+    }
+    t += gridDim.x * kWaves;
+    if (t < g.ntiles) {
+      L = tile_lane(g, t, lane);
+      pixel_load_public(a, L, pw);
     }
   }
 }
