@@ -219,21 +219,33 @@ __device__ __forceinline__ const uint4 &op(const LpLds<BF> &L, int table, int mt
   return L.t[table][(mt * 4 + s) * 64 + lane];
 }
 
+// Copies the operand tables into LDS, the first round of loads apart from its
+// stores (see AesFill): with 512 threads there is no other.
 template <bool BF>
-__device__ __forceinline__ void load_lp_tables(LpLds<BF> &L, const uint32_t *tables, int tid, int nthreads) {
-  const uint4 *src = reinterpret_cast<const uint4 *>(tables);
-  constexpr int kWords4 = kLpTableWords / 4;  // uint4 per table
-  for (int i = tid; i < kWords4; i += nthreads) {
-    if constexpr (BF) {
-      L.t[0][i] = src[2 * kWords4 + i];
-      L.t[1][i] = src[3 * kWords4 + i];
-      L.t[2][i] = src[4 * kWords4 + i];
-    } else {
-      L.t[0][i] = src[0 * kWords4 + i];
-      L.t[1][i] = src[1 * kWords4 + i];
+struct LpTableFill {
+  static constexpr int kFirst = BF ? 2 : 0;
+  static constexpr uint32_t kWords4 = kLpTableWords / 4;  // uint4 per table
+  u32x4 v0, v1, v2;
+  __device__ __forceinline__ void load(const uint32_t *tables, uint32_t tid) {
+    const u32x4 *src = reinterpret_cast<const u32x4 *>(tables) + kFirst * kWords4 + min(tid, kWords4 - 1u);
+    v0 = src[0];
+    v1 = src[kWords4];
+    if constexpr (BF) v2 = src[2 * kWords4];
+  }
+  __device__ __forceinline__ void store(LpLds<BF> &L, const uint32_t *tables, uint32_t tid, uint32_t nthreads) const {
+    u32x4 *dst = reinterpret_cast<u32x4 *>(&L.t[0][0]);
+    dst[tid] = v0;  // at most 512 threads
+    dst[kWords4 + tid] = v1;
+    if constexpr (BF) dst[2 * kWords4 + tid] = v2;
+    const u32x4 *src = reinterpret_cast<const u32x4 *>(tables) + kFirst * kWords4;
+    for (uint32_t i = tid + nthreads; i < kWords4; i += nthreads) {
+      dst[i] = src[i];
+      dst[kWords4 + i] = src[kWords4 + i];
+      if constexpr (BF) dst[2 * kWords4 + i] = src[2 * kWords4 + i];
     }
   }
-}
+};
+static_assert(kLpTableWords / 4 == 512, "one 16-byte word of a table per thread of the largest workgroup");
 
 // One lane's B operand of the int8 quantiser for one pass of up to 16
 // private coefficients (v_mfma_i32_16x16x64_i8, A = 16 blocks x 64 samples):
@@ -399,7 +411,7 @@ __device__ __forceinline__ void group_ctr(const TileGroup &G, const WaveLds &W, 
   const uint32_t total = n0 + (G.n > 1 ? (2u * npriv * G.nb1 + 15u) / 16u : 0u);
   const uint32_t rem = total & 63u;
   const uint32_t nrow = aes.enabled && rem != 0u && rem <= 16u ? total - rem : total;  // wave-uniform
-  for (uint32_t a = (uint32_t)lane; a < nrow; a += 64u) {
+  for (uint32_t a = fresh_lane(); a < nrow; a += 64u) {
     const bool second = a >= n0;
     const uint32_t i = second ? a - n0 : a;
     const uint32_t t = second ? G.t1 : G.t0;
@@ -439,14 +451,14 @@ __device__ __forceinline__ void group_ctr(const TileGroup &G, const WaveLds &W, 
 
 // The eight row words (columns 4h .. 4h + 3) of the lane's block in one half;
 // img spans the whole image (fewer than 2^32 samples), rows are W apart.
+// Lanes without a block take an offset beyond it, which loads zero.
 __device__ __forceinline__ void load_rows(const TileGeom &g, __amdgpu_buffer_rsrc_t img, uint32_t t, uint32_t nt,
-                                          int lane, uint32_t (&xr)[8]) {
-  const uint64_t b = (uint64_t)t * 64u + 32u * nt + ((uint32_t)lane & 31u);
-  const bool valid = b < g.nb;
-  const uint32_t voff = valid ? block_origin(g, (uint32_t)b) + 4u * (fresh_lane() >> 5) : 0u;
+                                          uint32_t (&xr)[8]) {
+  const uint32_t lane = fresh_lane();
+  const uint64_t b = (uint64_t)t * 64u + 32u * nt + (lane & 31u);
+  const uint32_t voff = b < g.nb ? block_origin(g, (uint32_t)b) + 4u * (lane >> 5) : 0xfffffff0u;
 #pragma unroll
-  for (int r = 0; r < 8; ++r)
-    xr[r] = valid ? __builtin_amdgcn_raw_buffer_load_b32(img, voff, (int)(r * g.W), kNonTemporal) : 0u;
+  for (int r = 0; r < 8; ++r) xr[r] = __builtin_amdgcn_raw_buffer_load_b32(img, voff, (int)(r * g.W), kNonTemporal);
 }
 
 // The one reconstruction routine: y[mt] (rows 4 mt .. 4 mt + 3 of the lane's
@@ -597,8 +609,19 @@ __global__ __launch_bounds__(512, lp_waves_per_eu<BF>()) void lp_frag_kernel(LpA
   RunSel rs{0u, 0u};
   if constexpr (!MP::kStatic) rs = run_sel(g.mask, lane, wave == 0u, s_rank[0]);
   LpQ2 *s_q2 = reinterpret_cast<LpQ2 *>(s_dyn + kRankBytes<MP>);
-  if (a.aes.enabled) aes_load_tables(s_aes, a.aes_t0, a.aes.key, threadIdx.x, blockDim.x);
-  load_lp_tables<BF>(s_tab, a.tables, threadIdx.x, blockDim.x);
+  // the tables' loads, then the first half's pixels, then the waits for the
+  // tables only (see AesFill)
+  uint32_t t = blockIdx.x * nw + wave;
+  const __amdgpu_buffer_rsrc_t img = buffer_rsrc(g.pix, (uint32_t)(g.nb * 64u));
+  AesFill fill;
+  LpTableFill<BF> tabs;
+  fill.load(a.aes_t0, a.aes.key, threadIdx.x);
+  tabs.load(a.tables, threadIdx.x);
+  uint32_t xn[8];  // the next half's pixel rows, in flight during the current half
+  load_rows(g, img, t, 0, xn);
+  __builtin_amdgcn_sched_barrier(0);
+  if (wave == 0u) fill.store(s_aes, threadIdx.x);
+  tabs.store(s_tab, a.tables, threadIdx.x, blockDim.x);
   for (uint32_t i = threadIdx.x; i < 64u * a.npass; i += blockDim.x) {
     const uint32_t rank = 16u * (i >> 6) + (i & 15u);
     const int n = rank < g.npriv ? (int)((a.plist[rank >> 2] >> (8u * (rank & 3u))) & 0xffu) : -1;
@@ -611,12 +634,8 @@ __global__ __launch_bounds__(512, lp_waves_per_eu<BF>()) void lp_frag_kernel(LpA
   const uint32_t h = (uint32_t)lane >> 5, jl = (uint32_t)lane & 31u;
   const uint32_t stride = gridDim.x * nw;
   const uint32_t npriv = g.npriv, npub = g.npub;
-  const __amdgpu_buffer_rsrc_t img = buffer_rsrc(g.pix, (uint32_t)(g.nb * 64u));
   const __amdgpu_buffer_rsrc_t res = buffer_rsrc(a.resid, (uint32_t)(g.nb * 16u));
 
-  uint32_t t = blockIdx.x * nw + wave;
-  uint32_t xn[8];  // the next half's pixel rows, in flight during the current half
-  if (t < g.ntiles) load_rows(g, img, t, 0, lane, xn);
   while (t < g.ntiles) {
     TileGroup G;
     G.n = 0;
@@ -641,20 +660,20 @@ __global__ __launch_bounds__(512, lp_waves_per_eu<BF>()) void lp_frag_kernel(LpA
         uint32_t xr[8];
 #pragma unroll
         for (int r = 0; r < 8; ++r) xr[r] = xn[r];
-        if (nt == 0) load_rows(g, img, t, 1, lane, xn);
-        else if (tn < g.ntiles) load_rows(g, img, tn, 0, lane, xn);
+        load_rows(g, img, nt == 0 ? t : tn, nt ^ 1u, xn);  // zero, unread, past the last tile
 
         // ---- private integers (int8 matrix products), into the stage
         {
           q2v4 a0, a1;
           lp_quant_operands(xr, a0, a1);
+          const uint32_t ql = fresh_lane();
           for (uint32_t p = 0; p < a.npass; ++p) {
-            const LpQ2 Q = s_q2[64u * p + lane];
-            const uint32_t rank = 16u * p + (uint32_t)(lane & 15);
+            const LpQ2 Q = s_q2[64u * p + ql];
+            const uint32_t rank = 16u * p + (ql & 15u);
 #pragma unroll
             for (int grp = 0; grp < 2; ++grp) {
               const q2v4 q = lp_quant(grp ? a1 : a0, Q);
-              const uint32_t blk = 32u * nt + 16u * grp + 4u * ((uint32_t)lane >> 4);
+              const uint32_t blk = 32u * nt + 16u * grp + 4u * (ql >> 4);
               if (rank < npriv)
                 *reinterpret_cast<uint2 *>(stage + 128u * rank + 2u * blk) =
                     make_uint2(__builtin_amdgcn_perm((uint32_t)q[1], (uint32_t)q[0], 0x05040100u),
@@ -820,14 +839,14 @@ __global__ __launch_bounds__(512, lp_waves_per_eu<BF>()) void lp_frag_kernel(LpA
         uint16_t *pub_tile = a.pub + b0 * npub;
         if (ntb == 64u) {
           const __amdgpu_buffer_rsrc_t prs = buffer_rsrc(pub_tile, npub * 128u);
-          for (uint32_t c = (uint32_t)lane; c < 4u * npub; c += 64u) {
+          for (uint32_t c = fresh_lane(); c < 4u * npub; c += 64u) {
             const uint4 v = *reinterpret_cast<const uint4 *>(W.pub + 16u * c);
             const u32x4 vv = {v.x, v.y, v.z, v.w};
             __builtin_amdgcn_raw_buffer_store_b128(vv, prs, 64u * npub * nt + 16u * c, 0, kNonTemporal);
           }
         } else {
           const uint32_t m0 = min(32u, ntb), nv = ntb > 32u * nt ? min(32u, ntb - 32u * nt) : 0u;
-          for (uint32_t c = (uint32_t)lane; c < 32u * npub; c += 64u) {
+          for (uint32_t c = fresh_lane(); c < 32u * npub; c += 64u) {
             const uint32_t r = c >> 5, j = c & 31u;
             if (j < nv)
               pub_tile[nt * npub * m0 + r * nv + j] = *reinterpret_cast<const uint16_t *>(W.pub + 64u * r + 2u * j);
@@ -847,6 +866,61 @@ __global__ __launch_bounds__(512, lp_waves_per_eu<BF>()) void lp_frag_kernel(LpA
 
 // ---------------------------------------------------------------------------
 // defrag
+// What a half of a tile reads from memory: the public values of the lane's
+// operand slots (one 16-bit value a register; private slots hold nothing of
+// use) and its residual codes.
+struct LpHalf {
+  uint32_t pv[32];
+  u32x2 code;
+};
+
+// Starts the loads of half nt of tile t.  Straight-line, so that the waits for
+// what was loaded earlier stay exact: with live = false (no such tile) the
+// buffers are empty and the loads return zero without a memory access.
+template <class MP>
+__device__ __forceinline__ void lp_load_half(const LpArgs &a, const RankTable *s_rank, bool live, uint32_t t, uint32_t nt,
+                                             int lane, LpHalf &H) {
+  const TileGeom &g = a.g;
+  const uint64_t b0 = (uint64_t)t * 64u;
+  const uint32_t ntb = live ? (uint32_t)min<uint64_t>(64u, g.nb - b0) : 0u;
+  const uint32_t h = (uint32_t)lane >> 5, jl = (uint32_t)lane & 31u, jb = 32u * nt + jl;
+  const __amdgpu_buffer_rsrc_t prs = buffer_rsrc(a.pub + b0 * g.npub, g.npub * ntb * 2u);
+  const __amdgpu_buffer_rsrc_t res = buffer_rsrc(a.resid + b0 * 16u, ntb * 16u);
+  H.code = __builtin_amdgcn_raw_buffer_load_b64(res, 16u * jb + 8u * h, 0, kNonTemporal);
+  // half-relative offsets: the half's region holds [rank][m blocks], and a
+  // pair's ranks are 4 apart for "DC + k AC"; lanes past the tile's last block
+  // read a neighbour's values or zero, never stored
+  const uint32_t m0 = min(32u, ntb), mh = nt ? (ntb > 32u ? ntb - 32u : 0u) : m0;
+  const uint32_t vbase = 2u * (nt * g.npub * m0 + jl);
+  if constexpr (MP::kStatic) {
+    const uint32_t vbase4 = vbase + 8u * mh * h;
+    static_for<0, 32>([&](auto rc) {
+      constexpr int slot = decltype(rc)::value;
+      const Pair<MP> P(8 * (slot / 4) + slot % 4, h);
+      if (P.any_pub)
+        H.pv[slot] = P.both_pub ? __builtin_amdgcn_raw_buffer_load_b16(prs, vbase4, (int)(2u * mh * P.c0.rank), 0)
+                                : __builtin_amdgcn_raw_buffer_load_b16(prs, vbase, (int)(2u * mh * P.c1.rank), 0);
+      else
+        H.pv[slot] = 0u;
+    });
+  } else {
+    const RankTable *rt = s_rank + opaque_zero();  // read per half: not 32 ranks held by the lane
+    const uint4 rk[2] = {rt->rank[h][0], rt->rank[h][1]};
+    const uint32_t *rw = reinterpret_cast<const uint32_t *>(rk);
+    static_for<0, 32>([&](auto rc) {
+      constexpr int slot = decltype(rc)::value;
+      const uint32_t row = (rw[slot / 4] >> (8 * (slot % 4))) & 0xffu;
+      H.pv[slot] = __builtin_amdgcn_raw_buffer_load_b16(prs, vbase + __umul24(row, 2u * mh), 0, 0);
+    });
+  }
+}
+
+// Each wave walks tiles; a half's loads are issued before the work on the half
+// (for a tile's first half: the decryption) that precedes it, so they are in
+// flight meanwhile; issued at their point of use, they were waited for twice a
+// tile.  With the tables' loads also apart from their stores, round trips of
+// 8192^2 at DC + 9 AC went from 126 to 121 us (fp16) and 138 to 126 (bf16), of
+// 2056 x 3000 from 29.6 to 27.4 (bf16).
 template <bool BF, class MP>
 __global__ __launch_bounds__(512, lp_waves_per_eu<BF>()) void lp_defrag_kernel(LpArgs a) {
   __shared__ AesLds s_aes;
@@ -858,99 +932,81 @@ __global__ __launch_bounds__(512, lp_waves_per_eu<BF>()) void lp_defrag_kernel(L
   const TileGeom &g = a.g;
   RankTable *s_rank = reinterpret_cast<RankTable *>(s_dyn);
   RunSel rs{0u, 0u};
-  if constexpr (!MP::kStatic) rs = run_sel(g.mask, lane, wave == 0u, s_rank[0]);
-  if (a.aes.enabled) aes_load_tables(s_aes, a.aes_t0, a.aes.key, threadIdx.x, blockDim.x);
-  load_lp_tables<BF>(s_tab, a.tables, threadIdx.x, blockDim.x);
+  if constexpr (!MP::kStatic) {
+    rs = run_sel(g.mask, lane, wave == 0u, s_rank[0]);
+    __syncthreads();
+  }
+  const uint32_t stride = gridDim.x * nw;
+  uint32_t t = blockIdx.x * nw + wave;
+  AesFill fill;
+  LpTableFill<BF> tabs;
+  fill.load(a.aes_t0, a.aes.key, threadIdx.x);
+  tabs.load(a.tables, threadIdx.x);
+  LpHalf H;
+  lp_load_half<MP>(a, s_rank, t < g.ntiles, min(t, g.ntiles - 1u), 0u, lane, H);
+  __builtin_amdgcn_sched_barrier(0);
+  if (wave == 0u) fill.store(s_aes, threadIdx.x);
+  tabs.store(s_tab, a.tables, threadIdx.x, blockDim.x);
   __syncthreads();
   WaveLds W;
   W.priv = s_dyn + kRankBytes<MP> + wave * a.wave_lds;
   W.pub = nullptr;
   const uint32_t h = (uint32_t)lane >> 5, jl = (uint32_t)lane & 31u;
-  const uint32_t stride = gridDim.x * nw;
-  const uint32_t npub = g.npub;
   const __amdgpu_buffer_rsrc_t img = buffer_rsrc(a.pix_out, (uint32_t)(g.nb * 64u));
-  const __amdgpu_buffer_rsrc_t res = buffer_rsrc(a.resid, (uint32_t)(g.nb * 16u));
 
-  for (uint32_t t0 = blockIdx.x * nw + wave; t0 < g.ntiles;) {
-    TileGroup G;
-    G.t0 = t0;
-    G.nb0 = (uint32_t)min<uint64_t>(64u, g.nb - (uint64_t)t0 * 64u);
-    G.t1 = t0 + stride;
-    G.n = kDefragGroup > 1 && G.t1 < g.ntiles ? 2u : 1u;
-    G.nb1 = G.n > 1 ? (uint32_t)min<uint64_t>(64u, g.nb - (uint64_t)G.t1 * 64u) : 0u;
-    t0 += G.n * stride;
+  for (; t < g.ntiles; t += stride) {
+    const uint64_t b0 = (uint64_t)t * 64u;
+    const uint32_t ntb = (uint32_t)min<uint64_t>(64u, g.nb - b0);
+    const TileGroup G{1u, t, t, ntb, 0u};
     group_ctr<false>(G, W, a.pstride, a.priv, g.npriv, lane, s_aes, a.aes);
     wave_lds_sync();
-    for (uint32_t gi = 0; gi < G.n; ++gi) {
-      const uint32_t t = gi ? G.t1 : G.t0, ntb = gi ? G.nb1 : G.nb0;
-      const uint64_t b0 = (uint64_t)t * 64u;
-      uint8_t *stage = W.priv + gi * a.pstride;
-      if (ntb < 64u) stage_repack<false>(stage, g.npriv, ntb, lane);
-      const __amdgpu_buffer_rsrc_t prs = buffer_rsrc(a.pub + b0 * npub, npub * ntb * 2u);
-      const uint32_t nexc = (uint32_t)__builtin_amdgcn_readfirstlane(a.exc.count[t]);
+    uint8_t *stage = W.priv;
+    if (ntb < 64u) stage_repack<false>(stage, g.npriv, ntb, lane);
+    const uint32_t nexc = (uint32_t)__builtin_amdgcn_readfirstlane(a.exc.count[t]);
 #pragma unroll 1
-      for (uint32_t nt = 0; nt < 2; ++nt) {
-        const uint32_t jb = 32u * nt + jl;
-        const bool bv = jb < ntb;
-        const uint32_t roff = 16u * (uint32_t)(b0 + jb) + 8u * h;
-        uint32_t code0 = 0u, code1 = 0u;
-        if (bv) {
-          const u32x2 cw = __builtin_amdgcn_raw_buffer_load_b64(res, roff, 0, kNonTemporal);
-          code0 = cw.x;
-          code1 = cw.y;
-        }
-        // ---- operands: public values straight from the fragment (half-
-        // relative offsets: the half's region holds [rank][m blocks], and the
-        // pair's ranks are 4 apart for "DC + k AC"), private integers from
-        // the decrypted stage
-        const uint32_t m0 = min(32u, ntb), mh = nt ? (ntb > 32u ? ntb - 32u : 0u) : m0;
-        const uint32_t vbase = 2u * (nt * npub * m0 + jl), vbase4 = vbase + 8u * mh * h;
-        uint4 chi[4], clo[4];
-        bool has_lo[4];
-        if constexpr (!MP::kStatic) {
-          const RankTable *rt = s_rank + opaque_zero();  // read per half: not 32 ranks held by the lane
-          const uint4 rk[2] = {rt->rank[h][0], rt->rank[h][1]};
-          const uint32_t *rw = reinterpret_cast<const uint32_t *>(rk);
-          uint32_t pv[32];
-          // private slots load some public value of the block, not used
-          static_for<0, 32>([&](auto rc) {
-            constexpr int slot = decltype(rc)::value;
-            const uint32_t row = (rw[slot / 4] >> (8 * (slot % 4))) & 0xffu;
-            pv[slot] = __builtin_amdgcn_raw_buffer_load_b16(prs, vbase + __umul24(row, 2u * mh), 0, 0);
-          });
-          static_for<0, 4>([&](auto sc) {
-            constexpr int s = decltype(sc)::value;
-            uint32_t hw[4], lw[4];
-            static_for<0, 4>([&](auto pc) {
-              constexpr int pr = decltype(pc)::value, slot0 = 8 * s + 2 * pr;
-              hw[pr] = pv[slot0] | (pv[slot0 + 1] << 16);
-              lw[pr] = 0u;
-              static_for<0, 2>([&](auto ec) {
-                constexpr int e = decltype(ec)::value, slot = slot0 + e;
-                if ((rs.any >> slot) & 1u) {
-                  const bool mine = (rs.mine >> slot) & 1u;
-                  const uint32_t row = (rw[slot / 4] >> (8 * (slot % 4))) & 0xffu;
-                  const int32_t q = (int32_t) * reinterpret_cast<const int16_t *>(stage + 128u * (mine ? row : 0u) + 2u * jb);
-                  merge_private<BF, e>(mine, q, hw[pr], lw[pr]);
-                }
-              });
-            });
-            chi[s] = make_uint4(hw[0], hw[1], hw[2], hw[3]);
-            clo[s] = make_uint4(lw[0], lw[1], lw[2], lw[3]);
-            has_lo[s] = BF && ((rs.any >> (8 * s)) & 0xffu) != 0u;
-          });
-        } else
+    for (uint32_t nt = 0; nt < 2; ++nt) {
+      const uint32_t jb = 32u * nt + jl;
+      const bool bv = jb < ntb;
+      // ---- operands: public values as loaded, private integers from the
+      // decrypted stage
+      uint4 chi[4], clo[4];
+      bool has_lo[4];
+      if constexpr (!MP::kStatic) {
+        const RankTable *rt = s_rank + opaque_zero();
+        const uint4 rk[2] = {rt->rank[h][0], rt->rank[h][1]};
+        const uint32_t *rw = reinterpret_cast<const uint32_t *>(rk);
         static_for<0, 4>([&](auto sc) {
-          constexpr int s = decltype(sc)::value, mt = s / 2, sg = s % 2;
+          constexpr int s = decltype(sc)::value;
+          uint32_t hw[4], lw[4];
+          static_for<0, 4>([&](auto pc) {
+            constexpr int pr = decltype(pc)::value, slot0 = 8 * s + 2 * pr;
+            hw[pr] = H.pv[slot0] | (H.pv[slot0 + 1] << 16);
+            lw[pr] = 0u;
+            static_for<0, 2>([&](auto ec) {
+              constexpr int e = decltype(ec)::value, slot = slot0 + e;
+              if ((rs.any >> slot) & 1u) {
+                const bool mine = (rs.mine >> slot) & 1u;
+                const uint32_t row = (rw[slot / 4] >> (8 * (slot % 4))) & 0xffu;
+                const int32_t q = (int32_t) * reinterpret_cast<const int16_t *>(stage + 128u * (mine ? row : 0u) + 2u * jb);
+                merge_private<BF, e>(mine, q, hw[pr], lw[pr]);
+              }
+            });
+          });
+          chi[s] = make_uint4(hw[0], hw[1], hw[2], hw[3]);
+          clo[s] = make_uint4(lw[0], lw[1], lw[2], lw[3]);
+          has_lo[s] = BF && ((rs.any >> (8 * s)) & 0xffu) != 0u;
+        });
+      } else {
+        static_for<0, 4>([&](auto sc) {
+          constexpr int s = decltype(sc)::value;
           uint32_t hw[4], lw[4];
           bool any_lo = false;
           static_for<0, 4>([&](auto pc) {
-            constexpr int pr = decltype(pc)::value;
-            constexpr int r0 = 8 * sg + 2 * pr;
+            constexpr int pr = decltype(pc)::value, slot0 = 8 * s + 2 * pr;
             uint32_t w = 0u, lo = 0u;
             static_for<0, 2>([&](auto ec) {
-              constexpr int e = decltype(ec)::value, r = r0 + e;
-              const Pair<MP> P(32 * mt + 8 * (r / 4) + (r % 4), h);
+              constexpr int e = decltype(ec)::value, slot = slot0 + e;
+              const Pair<MP> P(8 * (slot / 4) + slot % 4, h);
               uint32_t v = 0u;
               if (P.any_priv) {
                 const int32_t q = (int32_t) * reinterpret_cast<const int16_t *>(stage + P.priv_off(jb, h));
@@ -962,12 +1018,7 @@ __global__ __launch_bounds__(512, lp_waves_per_eu<BF>()) void lp_defrag_kernel(L
                 }
                 any_lo = true;
               }
-              if (P.any_pub) {
-                const uint32_t pv = P.both_pub
-                                        ? __builtin_amdgcn_raw_buffer_load_b16(prs, vbase4, (int)(2u * mh * P.c0.rank), 0)
-                                        : __builtin_amdgcn_raw_buffer_load_b16(prs, vbase, (int)(2u * mh * P.c1.rank), 0);
-                if (!P.mine_priv) v = pv;
-              }
+              if (P.any_pub && !P.mine_priv) v = H.pv[slot];
               w |= v << (16 * e);
             });
             hw[pr] = w;
@@ -977,32 +1028,35 @@ __global__ __launch_bounds__(512, lp_waves_per_eu<BF>()) void lp_defrag_kernel(L
           clo[s] = make_uint4(lw[0], lw[1], lw[2], lw[3]);
           has_lo[s] = BF && any_lo;
         });
-        f32x16 y[2];
-        lp_idct<BF>(s_tab, lane, chi, clo, has_lo, y);
-        uint32_t out[8];
+      }
+      const uint32_t code0 = H.code.x, code1 = H.code.y;
+      const bool more = nt == 0u || t + stride < g.ntiles;
+      lp_load_half<MP>(a, s_rank, more, nt == 0u ? t : min(t + stride, g.ntiles - 1u), nt ^ 1u, lane, H);
+      f32x16 y[2];
+      lp_idct<BF>(s_tab, lane, chi, clo, has_lo, y);
+      uint32_t out[8];
 #pragma unroll
-        for (int r = 0; r < 8; ++r) out[r] = rec_word(y[r / 4], r % 4);
-        if (__builtin_amdgcn_ballot_w64((code0 | code1) != 0u) != 0ull) {
+      for (int r = 0; r < 8; ++r) out[r] = rec_word(y[r / 4], r % 4);
+      if (__builtin_amdgcn_ballot_w64((code0 | code1) != 0u) != 0ull) {
 #pragma unroll
-          for (int r = 0; r < 8; ++r) out[r] = apply_codes(out[r], ((r < 4 ? code0 : code1) >> (2 * (r % 4))) & 0x03030303u);
+        for (int r = 0; r < 8; ++r) out[r] = apply_codes(out[r], ((r < 4 ? code0 : code1) >> (2 * (r % 4))) & 0x03030303u);
+      }
+      // samples kept in the exception slots (code 2), patched by the lane that owns them
+      for (uint32_t e = 0; e < min(nexc, a.exc.per_tile); ++e) {
+        const uint32_t pos = a.exc.pos[(size_t)t * a.exc.per_tile + e];
+        const uint32_t val = a.exc.val[(size_t)t * a.exc.per_tile + e];
+        const uint32_t p = pos & 63u;
+        if ((pos >> 6) == jb && ((p >> 2) & 1u) == h) {
+          const uint32_t r = p >> 3, c = p & 3u;
+#pragma unroll
+          for (int rr = 0; rr < 8; ++rr)
+            if ((uint32_t)rr == r) out[rr] = (out[rr] & ~(0xffu << (8u * c))) | (val << (8u * c));
         }
-        // samples kept in the exception slots (code 2), patched by the lane that owns them
-        for (uint32_t e = 0; e < min(nexc, a.exc.per_tile); ++e) {
-          const uint32_t pos = a.exc.pos[(size_t)t * a.exc.per_tile + e];
-          const uint32_t val = a.exc.val[(size_t)t * a.exc.per_tile + e];
-          const uint32_t p = pos & 63u;
-          if ((pos >> 6) == jb && ((p >> 2) & 1u) == h) {
-            const uint32_t r = p >> 3, c = p & 3u;
+      }
+      if (bv) {
+        const uint32_t voff = block_origin(g, (uint32_t)(b0 + jb)) + 4u * h;
 #pragma unroll
-            for (int rr = 0; rr < 8; ++rr)
-              if ((uint32_t)rr == r) out[rr] = (out[rr] & ~(0xffu << (8u * c))) | (val << (8u * c));
-          }
-        }
-        if (bv) {
-          const uint32_t voff = block_origin(g, (uint32_t)(b0 + jb)) + 4u * h;
-#pragma unroll
-          for (int r = 0; r < 8; ++r) __builtin_amdgcn_raw_buffer_store_b32(out[r], img, voff, (int)(r * g.W), kNonTemporal);
-        }
+        for (int r = 0; r < 8; ++r) __builtin_amdgcn_raw_buffer_store_b32(out[r], img, voff, (int)(r * g.W), kNonTemporal);
       }
     }
     wave_lds_sync();

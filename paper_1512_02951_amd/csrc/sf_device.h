@@ -208,22 +208,19 @@ __device__ __forceinline__ void aes_load_tables(AesLds &L, const uint32_t *__res
 // to store() is straight-line code: lanes without work load some valid address
 // instead of being branched round.
 struct AesFill {
-  uint4 v;
+  typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+  u32x4 v;
   uint32_t rk;
   __device__ __forceinline__ void load(const uint32_t *T0, const AesKey &K, uint32_t tid) {
-    v = reinterpret_cast<const uint4 *>(T0)[min(tid, 63u)];
+    v = reinterpret_cast<const u32x4 *>(T0)[min(tid, 63u)];
     rk = K.rk[min(tid, 43u)];
   }
-  __device__ __forceinline__ static uint4 rot(const uint4 &w, uint32_t n) {  // left by n bits
-    return make_uint4((w.x << n) | (w.x >> (32u - n)), (w.y << n) | (w.y >> (32u - n)),
-                      (w.z << n) | (w.z >> (32u - n)), (w.w << n) | (w.w >> (32u - n)));
-  }
   __device__ __forceinline__ void store(AesLds &L, uint32_t tid) const {
-    uint4 *t = reinterpret_cast<uint4 *>(L.t);
+    u32x4 *t = reinterpret_cast<u32x4 *>(L.t);
     t[tid] = v;
-    t[64 + tid] = rot(v, 8);
-    t[128 + tid] = rot(v, 16);
-    t[192 + tid] = rot(v, 24);
+    t[64 + tid] = (v << 8u) | (v >> 24u);
+    t[128 + tid] = (v << 16u) | (v >> 16u);
+    t[192 + tid] = (v << 24u) | (v >> 8u);
     if (tid < 44u) L.rk[tid] = rk;
   }
 };
