@@ -206,7 +206,8 @@ typedef struct sf_launch_shape {
                                and for defrag of 8 or more private
                                coefficients, else 2; reduced precision: the
                                largest that lets two workgroups share a
-                               compute unit's LDS)                          */
+                               compute unit's LDS; at most 2 for images of
+                               few tiles per compute unit)                  */
   uint32_t resident;        /* 1: one resident generation of workgroups
                                (as many as the device holds at once) loops
                                over the tiles (the default of the reduced

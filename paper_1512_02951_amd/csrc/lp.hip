@@ -1173,7 +1173,8 @@ size_t lp_lds_bytes(const Geom &g, int which, uint32_t waves) {
 }
 
 // Waves per workgroup: the largest of 8, 6, 4, 2, 1 whose LDS leaves room for
-// two workgroups per CU, else the largest that fits at all (0: none fits).
+// two workgroups per CU, else the largest that fits at all (0: none fits);
+// small images at most 2.
 uint32_t lp_default_waves(const DeviceState &ds, const Geom &g, int which) {
   static const uint32_t cand[] = {8, 6, 4, 2, 1};
   const size_t cu_lds = 160u * 1024u;
@@ -1182,7 +1183,7 @@ uint32_t lp_default_waves(const DeviceState &ds, const Geom &g, int which) {
       const size_t b = lp_lds_bytes(g, which, w);
       if (b > ds.max_lds_per_block) continue;
       if (pass == 0 && 2 * b > cu_lds) continue;
-      return w;
+      return small_image(ds, g, which) && w > 2u ? 2u : w;
     }
   return 0;
 }

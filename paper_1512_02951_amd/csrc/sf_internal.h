@@ -110,10 +110,24 @@ uint32_t lp_default_waves(const DeviceState &ds, const Geom &g, int which);
 // for the lighter ones (measured on the 4096^2 RGB DC + 5 AC and the 8192^2
 // DC + 9 AC workloads).
 inline bool plain_heavy(const Geom &g) { return g.npriv >= 8; }
+// Images of few tiles per compute unit (each wavefront then has one tile,
+// whatever the workgroup): 2 wavefronts per workgroup, so that the tiles
+// spread over more compute units.  At 1024^2, DC + 9 AC (one tile per CU):
+// FP32 frag 10.4 us with 4 waves, 9.3 with 2, defrag 8.6 / 7.5; bf16 frag 14.7
+// with 8, 11.9 with 2, defrag 11.6 / 8.2.  The line: FP32 at four per CU (2048 x
+// 2040) is slower with 2 (round trip 20.3 / 21.1), the precision frag at six
+// (2056 x 3000) is not faster (16.0 / 16.5), its defrag there still is
+// (13.3 / 11.9).
+inline bool small_image(const DeviceState &ds, const Geom &g, int which) {
+  const uint32_t per_cu = g.precision == SF_FP32 ? 2u : which == 0 ? 4u : 8u;
+  return g.ntiles <= per_cu * (uint32_t)ds.num_cu;
+}
 // Default waves per workgroup of the plain kernels: frag 4 (one tile each,
 // up to 5 resident per SIMD by registers and LDS), defrag 4 from 8 private
-// coefficients on, else 2.
-inline uint32_t plain_default_waves(const Geom &g, int which) { return which == 0 || plain_heavy(g) ? 4u : 2u; }
+// coefficients on, else 2; small images 2.
+inline uint32_t plain_default_waves(const DeviceState &ds, const Geom &g, int which) {
+  return (which == 0 || plain_heavy(g)) && !small_image(ds, g, which) ? 4u : 2u;
+}
 
 // Launchers (plain.hip, aes.hip).
 int launch_frag_fp32(const DeviceState &ds, const Geom &g, const uint8_t *pix, float *pub, uint8_t *priv,
