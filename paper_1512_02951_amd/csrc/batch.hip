@@ -210,7 +210,8 @@ __global__ __launch_bounds__(kThreads, 3) void frag_batch_kernel(BatchArgs a) {
   uint8_t *lp = s_dyn + wave * (a.lds_priv_bytes + kBatchQ2Bytes);
   uint8_t *stage = lp + a.lds_priv_bytes;
   Q2Operands *wq = reinterpret_cast<Q2Operands *>(stage + kQ2StageBytes);
-  uint64_t qmask = 0;  // mask whose operands wq holds (masks are never 0)
+  uint64_t qmask = 0;  // mask whose operands wq and rc hold (masks are never 0)
+  RankCert rc{};
   // the body must be inlined: its buffer resources and table pointers live in
   // scalar registers, which an outlined call could not guarantee
   batch_loop<kSched>(a.ws, a.n, 0, a.tiles_per_grab, lane, [&](uint32_t t, const BatchDesc &d) __attribute__((always_inline)) {
@@ -231,11 +232,13 @@ __global__ __launch_bounds__(kThreads, 3) void frag_batch_kernel(BatchArgs a) {
       if (mfma_q2) {
         if (d.g.mask != qmask) {
           wave_lds_sync();
-          wq[lane] = q2_operands(a.q2, private_ac<MP>(d.g.mask, lane & 15), lane);
+          wq[lane] = q2_operands(a.q2, private_ac<MP>(d.g.mask, lane), lane);
+          if constexpr (!MP::kStatic) rc = rank_cert(a.q2, d.g.mask, lane);
           wave_lds_sync();
           qmask = d.g.mask;
         }
-        frag_tile<MP, true>(d.g, o, t, L, xs, lane, lp, s_aes, enc, d.ctr_hi, d.ctr_lo, a.K, stage, &wq[lane]);
+        frag_tile<MP, true>(d.g, o, t, L, xs, lane, lp, s_aes, enc, d.ctr_hi, d.ctr_lo, a.K, stage, &wq[lane],
+                            NoPrefetch{}, rc);
       } else {
         frag_tile<MP, false>(d.g, o, t, L, xs, lane, lp, s_aes, enc, d.ctr_hi, d.ctr_lo, a.K);
       }

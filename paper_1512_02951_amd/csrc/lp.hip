@@ -260,15 +260,15 @@ struct LpQ2 {
   int32_t pad;
 };
 
-__device__ __forceinline__ LpQ2 lp_q2_operand(const uint32_t *q2, int n, int lane) {
+__device__ __forceinline__ LpQ2 lp_q2_operand(const uint32_t *q2, int z, int lane) {
   LpQ2 o;
   const int g = lane >> 4;
 #pragma unroll
   for (int L = 0; L < 3; ++L)
 #pragma unroll
     for (int r = 0; r < 4; ++r)
-      o.limb[L][r] = n >= 0 ? (int)q2[n * kQ2RowWords + 16 * L + 2 * (4 * (g >> 1) + r) + (g & 1)] : 0;
-  const int32_t bias = n >= 0 ? (int32_t)q2[n * kQ2RowWords + 48] : 0;
+      o.limb[L][r] = z >= 0 ? (int)q2[z * kQ2RowWords + 16 * L + 2 * (4 * (g >> 1) + r) + (g & 1)] : 0;
+  const int32_t bias = z >= 0 ? (int32_t)q2[z * kQ2RowWords + 48] : 0;
   o.beta[0] = bias & 0xff;
   o.beta[1] = (bias >> 8) & 0xff;
   o.beta[2] = bias >> 16;
@@ -335,7 +335,7 @@ struct LpArgs {
   uint32_t npass;          // int8 quantiser passes, ceil(npriv / 16)
   uint32_t pstride;        // LDS bytes of one tile's private stage
   uint32_t wave_lds;       // LDS bytes per wave
-  uint32_t plist[16];      // natural indices of the private positions, 4 per word
+  uint32_t plist[16];      // zigzag positions of the private coefficients, 4 per word
 };
 
 // LDS of one wave: one private stage per tile of its group (int16
@@ -624,8 +624,8 @@ __global__ __launch_bounds__(512, lp_waves_per_eu<BF>()) void lp_frag_kernel(LpA
   tabs.store(s_tab, a.tables, threadIdx.x, blockDim.x);
   for (uint32_t i = threadIdx.x; i < 64u * a.npass; i += blockDim.x) {
     const uint32_t rank = 16u * (i >> 6) + (i & 15u);
-    const int n = rank < g.npriv ? (int)((a.plist[rank >> 2] >> (8u * (rank & 3u))) & 0xffu) : -1;
-    s_q2[i] = lp_q2_operand(a.q2, n, (int)(i & 63u));
+    const int z = rank < g.npriv ? (int)((a.plist[rank >> 2] >> (8u * (rank & 3u))) & 0xffu) : -1;
+    s_q2[i] = lp_q2_operand(a.q2, z, (int)(i & 63u));
   }
   __syncthreads();
   WaveLds W;
@@ -1156,10 +1156,9 @@ LpArgs lp_args(const DeviceState &ds, const Geom &g, const uint8_t *pix, const s
   a.npass = (g.npriv + 15u) / 16u;
   a.pstride = (2u * g.npriv * 64u + 15u) & ~15u;
   int i = 0;
-  static constexpr ZigZag zz{};
   for (int z = 0; z < 64; ++z)
     if ((g.mask >> z) & 1u) {
-      a.plist[i >> 2] |= (uint32_t)zz.nat[z] << (8 * (i & 3));
+      a.plist[i >> 2] |= (uint32_t)z << (8 * (i & 3));
       ++i;
     }
   return a;

@@ -235,7 +235,7 @@ __global__ __launch_bounds__(kThreads) void pixel_frag_kernel(PixArgs a) {
   const TileGeom &g = a.g;
   uint32_t t = blockIdx.x * kWaves + wave;
   AesFill fill;
-  const int first = wave == 0u ? private_ac<MP>(g.mask, lane & 15) : -1;
+  const int first = wave == 0u ? private_ac<MP>(g.mask, lane) : -1;
   fill.load(a.aes_t0, a.aes.key, threadIdx.x);
   const Q2Operands q2op = q2_operands(a.q2, first, lane);
   TileLane L = tile_lane(g, min(t, g.ntiles - 1u), lane);

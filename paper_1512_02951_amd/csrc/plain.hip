@@ -66,9 +66,11 @@ __global__ __launch_bounds__(kMaxThreads, SF_FRAG_WAVES_PER_EU) void frag_fp32_k
   // DC + 5 AC 20.7 -> 20.0 us; 4096^2 RGB 83.3 -> 81.2).
   AesFill fill;
   Q2Operands q2op;
-  const int first = threadIdx.x < 64 ? private_ac<MP>(a.g.mask, lane & 15) : -1;
+  const int first = threadIdx.x < 64 ? private_ac<MP>(a.g.mask, lane) : -1;
   fill.load(a.aes_t0, a.aes.key, threadIdx.x);
   if constexpr (kQ2Mfma) q2op = q2_operands(a.o.q2, first, lane);
+  RankCert rc{};
+  if constexpr (!MP::kStatic && kQ2Mfma) rc = rank_cert(a.o.q2, a.g.mask, lane);
   TileLane L = tile_lane(a.g, min(t, a.g.ntiles - 1u), lane);
   uint32_t xs[16];
   load_block(a.g, L, xs);
@@ -81,7 +83,7 @@ __global__ __launch_bounds__(kMaxThreads, SF_FRAG_WAVES_PER_EU) void frag_fp32_k
   if (t >= a.g.ntiles) return;
   if constexpr (!kLoop) {
     frag_tile<MP, kQ2Mfma>(a.g, a.o, t, L, xs, lane, lp, s_aes, a.aes.enabled, a.aes.ctr_hi, a.aes.ctr_lo, a.K,
-                           q2stage, Q);
+                           q2stage, Q, NoPrefetch{}, rc);
     return;
   }
   if constexpr (kQ2Mfma) {
@@ -92,9 +94,11 @@ __global__ __launch_bounds__(kMaxThreads, SF_FRAG_WAVES_PER_EU) void frag_fp32_k
       const bool more = tn < a.g.ntiles;
       const TileLane Ln = more ? tile_lane(a.g, tn, lane) : L;
       frag_tile<MP, true>(a.g, a.o, t, L, xs, lane, lp, s_aes, a.aes.enabled, a.aes.ctr_hi, a.aes.ctr_lo, a.K,
-                          q2stage, Q, [&]() {
+                          q2stage, Q,
+                          [&]() {
                             if (more) load_block(a.g, Ln, xs);
-                          });
+                          },
+                          rc);
       if (!more) break;
       t = tn;
       L = Ln;

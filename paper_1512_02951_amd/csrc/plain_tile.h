@@ -146,6 +146,7 @@ __device__ __forceinline__ uint64_t opaque_u64(uint64_t v) {
 // for every zigzag position, n = natural index of the position.
 template <class MP, class FP, class FQ>
 __device__ __forceinline__ void for_each_coef(uint64_t mask, FP &&fpriv, FQ &&fpub) {
+  uint32_t pr = 0;  // run-time selections: private positions before z
   static_for<0, 64>([&](auto zc) {
     constexpr int z = decltype(zc)::value;
     constexpr int n = kZigZag.nat[z];
@@ -153,9 +154,10 @@ __device__ __forceinline__ void for_each_coef(uint64_t mask, FP &&fpriv, FQ &&fp
       if constexpr (z < MP::kNPriv) fpriv(std::integral_constant<int, n>{}, (uint32_t)z);
       else fpub(std::integral_constant<int, n>{}, (uint32_t)(z - MP::kNPriv));
     } else {
-      const uint32_t pr = (uint32_t)__builtin_popcountll(mask & ((1ull << z) - 1ull));
-      if ((mask >> z) & 1u) fpriv(std::integral_constant<int, n>{}, pr);
+      const uint32_t bit = (uint32_t)(mask >> z) & 1u;
+      if (bit) fpriv(std::integral_constant<int, n>{}, pr);
       else fpub(std::integral_constant<int, n>{}, (uint32_t)z - pr);
+      pr += bit;
     }
   });
 }
@@ -217,36 +219,53 @@ struct Q2Operands {
   uint32_t bias;  // 128 sum_p Bq of that column
 };
 
-// Natural index of the a-th private AC coefficient (zigzag order), -1 if none.
+// Run-time selections: lane r gets the zigzag position of the private
+// coefficient of rank r (lanes from their number on: anything).  The lane whose
+// position it is pushes it there.  Called by the whole wave; fewer than 64
+// private positions.
+__device__ __forceinline__ uint32_t rank_to_zigzag(uint64_t mask, int lane) {
+  const uint32_t rank = (uint32_t)__builtin_popcountll(mask & ((1ull << lane) - 1ull));
+  const uint32_t to = (mask >> lane) & 1u ? rank : 63u;
+  return (uint32_t)__builtin_amdgcn_ds_permute((int)(4u * to), lane) & 63u;
+}
+
+// Zigzag position of the (lane % 16)-th private AC coefficient, -1 if none.
+// Called by the whole wave.
 template <class MP>
-__device__ __forceinline__ int private_ac(uint64_t mask, int a) {
-  int n = -1, seen = 0;
-  static_for<1, 64>([&](auto zc) {
-    constexpr int z = decltype(zc)::value;
-    bool priv;
-    if constexpr (MP::kStatic) priv = z < MP::kNPriv;
-    else priv = (mask >> z) & 1u;
-    if (priv) {
-      if (seen == a) n = kZigZag.nat[z];
-      ++seen;
-    }
-  });
-  return n;
+__device__ __forceinline__ int private_ac(uint64_t mask, int lane) {
+  const int a = lane & 15;
+  if constexpr (MP::kStatic) {
+    return a + 1 < MP::kNPriv ? a + 1 : -1;
+  } else {
+    const int rank = a + (int)(mask & 1u);
+    const int z = __builtin_amdgcn_ds_bpermute(4 * rank, (int)rank_to_zigzag(mask, lane));
+    return rank < __builtin_popcountll(mask) ? z : -1;
+  }
+}
+
+// Run-time selections with at most 16 AC coefficients: E and M of the
+// certificate (table words kQ2Cert*) of the private coefficient of rank = lane.
+struct RankCert {
+  float e, m;
+};
+__device__ __forceinline__ RankCert rank_cert(const uint32_t *q2, uint64_t mask, int lane) {
+  const uint32_t *row = q2 + rank_to_zigzag(mask, lane) * kQ2RowWords;
+  return RankCert{__uint_as_float(row[kQ2CertE]), __uint_as_float(row[kQ2CertM])};
 }
 
 // Straight-line (see AesFill): columns without a coefficient load row 0.
-__device__ __forceinline__ Q2Operands q2_operands(const uint32_t *q2, int n, int lane) {
+__device__ __forceinline__ Q2Operands q2_operands(const uint32_t *q2, int z, int lane) {
   Q2Operands o;
   static_assert(kQ2RowWords % 4 == 0, "rows of whole 16-byte words");
-  const uint32_t *row = q2 + (n >= 0 ? n * kQ2RowWords : 0);
+  const uint32_t *row = q2 + (z >= 0 ? z * kQ2RowWords : 0);
 #pragma unroll
   for (int L = 0; L < 3; ++L) {
     const q2v4 v = *reinterpret_cast<const q2v4 *>(row + 16 * L + 4 * (lane >> 4));
 #pragma unroll
-    for (int j = 0; j < 4; ++j) o.b[L][j] = n >= 0 ? v[j] : 0;
+    for (int j = 0; j < 4; ++j) o.b[L][j] = z >= 0 ? v[j] : 0;
   }
   const uint32_t bias = row[48];
-  o.bias = n >= 0 ? bias : 0u;
+  o.bias = z >= 0 ? bias : 0u;
   return o;
 }
 
@@ -501,7 +520,13 @@ template <class MP, bool kQ2Mfma = false, class PF = NoPrefetch>
 __device__ __forceinline__ void frag_tile(const TileGeom &g, const FragOut &o, uint32_t t, const TileLane &L,
                                           uint32_t (&xs)[16], int lane, uint8_t *lp, const AesLds &s_aes, uint32_t enc,
                                           uint64_t ctr_hi, uint64_t ctr_lo, const DctK &K, uint8_t *q2stage = nullptr,
-                                          const Q2Operands *Q = nullptr, PF &&prefetch = PF{}) {
+                                          const Q2Operands *Q = nullptr, PF &&prefetch = PF{},
+                                          const RankCert &rc = RankCert{}) {
+  // run-time selections on the matrix cores: the private part by rank (no
+  // scalar table loads one after another, no rank arithmetic), then the public
+  // stores, one wave-uniform branch around each.  8192^2, six private positions
+  // that are no prefix: round trip 148 -> 118 us; 1080 x 1920 RGB 28.4 -> 24.7
+  constexpr bool kByRank = !MP::kStatic && kQ2Mfma;
   const uint64_t b0 = L.b0;
   const uint32_t nt = L.nt;
   const bool valid = L.valid != 0u;
@@ -525,7 +550,9 @@ __device__ __forceinline__ void frag_tile(const TileGeom &g, const FragOut &o, u
 
   // ---- zigzag split
   const __amdgpu_buffer_rsrc_t pub_rs = buffer_rsrc(o.pub + b0 * g.npub, g.npub * nt * 4u);
-  const int pub_voff = lane * 4;
+  // run-time selections: lanes without a block take an offset beyond the
+  // buffer, where stores are dropped, instead of a branch at every position
+  const int pub_voff = MP::kStatic || valid ? lane * 4 : (int)0xfffffff0u;
   const cu32_ptr q2 = as_const(o.q2) + opaque_zero();
   // cert = sum over private n of (|q_n - acc_n / 2^20| + E_n) * M_n bounds how far
   // the private rounding moves any reconstructed sample (table words kQ2Cert*).
@@ -534,10 +561,36 @@ __device__ __forceinline__ void frag_tile(const TileGeom &g, const FragOut &o, u
   // rounding d_n = q_n - acc_n / 2^20 (exact in FP32) and sum_n E_n M_n
   float dq[64];
   float sum_em = 0.0f;
+  if constexpr (kByRank) {
+    const uint32_t np = (uint32_t)__builtin_amdgcn_readfirstlane((int)g.npriv);
+    static_for<0, kQ2MfmaMaxAc + 1>([&](auto rcc) {
+      constexpr uint32_t r = decltype(rcc)::value;
+      if (r < np) {
+        int32_t q;
+        if (r == 0 && dc_priv) {
+          q = (int32_t)((S + 3u + ((S >> 3) & 1u)) >> 3);  // as below
+          const int32_t d = 8 * q - (int32_t)S;
+          cert += (float)(d < 0 ? -d : d) * (0.125f * 0.125f);
+        } else {
+          const int32_t acc = q2_mfma_acc(q2stage, r - dc_priv, lane);
+          q = q2_round(acc);
+          const int32_t d = (int32_t)((uint32_t)q << 20) - acc;
+          const float E = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(rc.e), r));
+          const float M = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(rc.m), r));
+          cert = __builtin_fmaf(__builtin_fmaf((float)(d < 0 ? -d : d), 0x1p-20f, E), M, cert);
+        }
+        if (valid) *reinterpret_cast<int16_t *>(lp + 2u * (r * nt + lane)) = (int16_t)q;
+      }
+    });
+  }
   for_each_coef<MP>(
       mask,
       [&](auto nc, uint32_t pr) {
         constexpr int n = decltype(nc)::value;
+        if constexpr (kByRank) {  // the lane's own integer, for the check below
+          if (o.exc.check) c[n] = (float)*reinterpret_cast<const int16_t *>(lp + 2u * (pr * nt + lane));
+          return;
+        }
         int32_t q;
         if constexpr (n == 0) {
           q = (int32_t)((S + 3u + ((S >> 3) & 1u)) >> 3);  // round half even of S / 8
@@ -545,7 +598,7 @@ __device__ __forceinline__ void frag_tile(const TileGeom &g, const FragOut &o, u
           cert += (float)(d < 0 ? -d : d) * (0.125f * 0.125f);  // M_0 = 1/8, E_0 = 0
           dq[0] = (float)d * 0.125f;
         } else {
-          const cu32_ptr row = q2 + n * kQ2RowWords;
+          const cu32_ptr row = q2 + kZigZagInv.pos[n] * kQ2RowWords;
           int32_t acc;
           if constexpr (kQ2Mfma) acc = q2_mfma_acc(q2stage, pr - dc_priv, lane);
           else acc = q2_acc(xs, row);
@@ -563,7 +616,7 @@ __device__ __forceinline__ void frag_tile(const TileGeom &g, const FragOut &o, u
       },
       [&](auto nc, uint32_t pu) {
         constexpr int n = decltype(nc)::value;
-        if (valid)
+        if (!MP::kStatic || valid)
           __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(c[n]), pub_rs, pub_voff, (int)(pu * nt * 4u), kNonTemporal);
       });
 

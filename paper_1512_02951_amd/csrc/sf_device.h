@@ -132,7 +132,7 @@ __device__ __forceinline__ void idct8x8(float (&c)[64], const DctK &K) {
 // D_* = sum_p (x_p - 128) * limb_p, evaluated with 4-way int8 dot products on
 // the packed pixel words.  All arithmetic is modulo 2^32; the exact result
 // |acc| <= 2040 * 2^20 < 2^31 fits, so the wrapped value is exact.
-// Table row layout (kQ2RowWords words per natural index n):
+// Table row layout (kQ2RowWords words per zigzag position of n):
 //   [0,16) limb l, [16,32) limb m, [32,48) limb h (4 signed bytes per word,
 //   byte i of word w is pixel p = 4w + i), [48] = 128 * sum_p Bq[n][p],
 //   [49] = E_n as float bits: 255 * sum_p |Bq[n][p]/2^20 - B[n][p]| (>= |acc/2^20 - C_n|),

@@ -59,6 +59,7 @@ void build_dct(HostTables &t) {
   t.dct.c3 = (float)(0.5L * cosl(3.0L * pi / 16.0L));
   t.dct.c5 = (float)(0.5L * cosl(5.0L * pi / 16.0L));
   t.dct.c7 = (float)(0.5L * cosl(7.0L * pi / 16.0L));
+  static constexpr ZigZagInv zzi{};
   for (int u = 0; u < 8; ++u)
     for (int v = 0; v < 8; ++v) {
       const int n = 8 * u + v;
@@ -80,7 +81,7 @@ void build_dct(HostTables &t) {
       t.cert_m[n] = nextafterf((float)maxabs, 1.0f);
       t.cert_e[n] = nextafterf((float)(255.0L * ldexpl(errsum, -20)), 1.0f);
       // signed-byte limbs of every entry, 4 pixels per word
-      uint32_t *row = &t.q2[n * kQ2RowWords];
+      uint32_t *row = &t.q2[zzi.pos[n] * kQ2RowWords];
       memset(row, 0, sizeof(uint32_t) * kQ2RowWords);
       for (int p = 0; p < 64; ++p) {
         int32_t q = qi[p];

@@ -98,6 +98,15 @@ def test_runtime_masks(mask):
     _check(x, mask, synth.aes_key(1), synth.ctr0(1, 9), "runtime mask")
 
 
+@pytest.mark.parametrize("mask", [0x9F, (1 << 17) - 1, (1 << 17) - 2, (1 << 18) - 1, (1 << 18) - 2, 1 << 63,
+                                  0x8421084210842101])
+def test_runtime_masks_at_the_matrix_quantiser_limit(mask):
+    # 16 private AC coefficients (one matrix operand column each) with and
+    # without DC, 17 (the vector quantiser), one; a partial last tile
+    x = np.concatenate([_adversarial(1)[:, :, :56], synth.image(64, 56, 1, 1, 3).numpy()])
+    _check(x, mask, synth.aes_key(1), synth.ctr0(1, 3), "quantiser limit")
+
+
 @pytest.mark.parametrize("k", [2, 5, 9, 20])
 def test_adversarial_blocks_and_clear_private(k):
     x = _adversarial(2)
