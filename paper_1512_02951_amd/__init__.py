@@ -12,6 +12,7 @@ Entry points (same names as the C ABI): :func:`frag_image`,
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
 from dataclasses import dataclass
 
@@ -105,18 +106,38 @@ def desc(H: int, W: int, C: int, mask: int, precision="fp32") -> SfDesc:
 def aes_ctr(key: bytes | None, ctr0: bytes | None):
     if key is None:
         return None
-    a = SfAesCtr()
-    a.key[:] = list(bytes(key))
-    a.ctr0[:] = list(bytes(ctr0 if ctr0 is not None else bytes(16)))
-    return a
+    k, c = bytes(key), bytes(ctr0) if ctr0 is not None else bytes(16)
+    if len(k) != 16 or len(c) != 16:
+        raise ValueError("AES-128 key and initial counter block must be 16 bytes each")
+    return SfAesCtr.from_buffer_copy(k + c)
 
 
-def fragment_sizes(H: int, W: int, C: int, mask: int, precision="fp32"):
-    """(public_bytes, private_bytes, residual_bytes) for an image; host only."""
+# Pure functions of their arguments that every call needs: computed once per
+# image shape and selection in use (a small call's time is mostly host work).
+@functools.lru_cache(maxsize=256, typed=True)
+def _desc(H: int, W: int, C: int, mask: int, precision) -> SfDesc:
+    return desc(H, W, C, mask, precision)
+
+
+@functools.lru_cache(maxsize=256, typed=True)
+def _fragment_sizes(H: int, W: int, C: int, mask: int, precision):
     d = desc(H, W, C, mask, precision)
     pb, qb, rb = ctypes.c_size_t(), ctypes.c_size_t(), ctypes.c_size_t()
     check(lib().sf_fragment_sizes(ctypes.byref(d), ctypes.byref(pb), ctypes.byref(qb), ctypes.byref(rb)))
     return pb.value, qb.value, rb.value
+
+
+@functools.lru_cache(maxsize=256, typed=True)
+def _exception_bytes(H: int, W: int, C: int, mask: int, per_tile: int, precision):
+    d = desc(H, W, C, mask, precision)
+    nbytes, needed = ctypes.c_size_t(), ctypes.c_int()
+    check(lib().sf_exception_bytes(ctypes.byref(d), per_tile, ctypes.byref(nbytes), ctypes.byref(needed)))
+    return nbytes.value, bool(needed.value)
+
+
+def fragment_sizes(H: int, W: int, C: int, mask: int, precision="fp32"):
+    """(public_bytes, private_bytes, residual_bytes) for an image; host only."""
+    return _fragment_sizes(H, W, C, mask, precision)
 
 
 def prefix_mask(k: int) -> int:
@@ -125,24 +146,20 @@ def prefix_mask(k: int) -> int:
 
 
 def _stream(stream):
-    import torch
+    """The stream's raw handle, as an argument of the library's functions."""
     if stream is None:
-        return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
-    if isinstance(stream, int):
-        return ctypes.c_void_p(stream)
-    return ctypes.c_void_p(stream.cuda_stream)
+        import torch
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    return stream if isinstance(stream, int) else stream.cuda_stream
 
 
 def _ptr(t):
-    return ctypes.c_void_p(t.data_ptr()) if t is not None else None
+    return t.data_ptr() if t is not None else None
 
 
 def exception_bytes(H: int, W: int, C: int, mask: int, per_tile: int, precision="fp32"):
     """(bytes, needed) of an exception buffer; host only."""
-    d = desc(H, W, C, mask, precision)
-    nbytes, needed = ctypes.c_size_t(), ctypes.c_int()
-    check(lib().sf_exception_bytes(ctypes.byref(d), per_tile, ctypes.byref(nbytes), ctypes.byref(needed)))
-    return nbytes.value, bool(needed.value)
+    return _exception_bytes(H, W, C, mask, per_tile, precision)
 
 
 DEFAULT_PER_TILE = 64
@@ -227,7 +244,7 @@ def frag_image(pixels, mask: int, key: bytes | None = None, ctr0: bytes | None =
             exceptions=ExceptionList.empty((C, H, W), mask, device=pixels.device, precision=prec),
             residual=torch.empty(rb, dtype=torch.uint8, device=pixels.device) if rb else None,
             shape=(C, H, W), mask=mask, precision=prec)
-    d = desc(H, W, C, mask, prec)
+    d = _desc(H, W, C, mask, prec)
     exc = out.exceptions.c() if out.exceptions is not None else None
     rc = lib().frag_image(ctypes.byref(d), _ptr(pixels), _ptr(out.public), _ptr(out.private),
                           ctypes.byref(exc) if exc is not None else None, _ptr(out.residual),
@@ -244,7 +261,7 @@ def defrag_image(frags: Fragments, key: bytes | None = None, ctr0: bytes | None 
     C, H, W = frags.shape
     if out is None:
         out = torch.empty((C, H, W), dtype=torch.uint8, device=frags.private.device)
-    d = desc(H, W, C, frags.mask, frags.precision)
+    d = _desc(H, W, C, frags.mask, frags.precision)
     exc = frags.exceptions.c() if frags.exceptions is not None else None
     rc = lib().defrag_image(ctypes.byref(d), _ptr(frags.public), _ptr(frags.private),
                             ctypes.byref(exc) if exc is not None else None, _ptr(frags.residual),

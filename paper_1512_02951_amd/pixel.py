@@ -5,6 +5,7 @@ run in the HIP library."""
 from __future__ import annotations
 
 import ctypes
+import functools
 from dataclasses import dataclass
 
 from . import SfAesCtr, SfDesc, aes_ctr, check, desc, lib as _base_lib, _stream
@@ -41,6 +42,11 @@ def _flags(strong: bool, storage_bits: int) -> int:
 
 def fragment_sizes(H: int, W: int, C: int, mask: int, strong: bool = False, storage_bits: int = 11):
     """(public_bytes, private_bytes); host only."""
+    return _fragment_sizes(H, W, C, mask, strong, storage_bits)
+
+
+@functools.lru_cache(maxsize=256, typed=True)
+def _fragment_sizes(H, W, C, mask, strong, storage_bits):
     d = desc(H, W, C, mask)
     pb, qb = ctypes.c_size_t(), ctypes.c_size_t()
     check(lib().sf_pixel_fragment_sizes(ctypes.byref(d), _flags(strong, storage_bits), ctypes.byref(pb),
