@@ -127,9 +127,11 @@ __device__ __forceinline__ void sha512_round(uint64_t (&v)[8], uint64_t kw) {
 // SHA-512 of a message of 2 np bytes (np <= 16): the private integers as
 // int16 little-endian.  One 1024-bit block: message, the 0x80 byte, zeros,
 // the bit length in the last word.  Returns the digest words H[0..7].
-// Rounds 0..15 are unrolled (most message words are constants there); rounds
-// 16..79 run as a loop of 16 unrolled rounds that extends the schedule in
-// place, which keeps the code and the live schedule words small.
+// Rounds 0..15 are unrolled (most message words are constants there), and
+// rounds 16..31 (most terms of their schedule words are zero or constant; with
+// them in the loop, a 4096^2 RGB round trip took 189 us, now 174); rounds 32..79 run as a loop of 16 unrolled
+// rounds that extends the schedule in place, which keeps the code and the live
+// schedule words small.
 template <int NP>
 __device__ __forceinline__ void sha512_private(const int32_t (&q)[kPixMaxPriv], uint32_t np_rt, uint64_t (&Hout)[8]) {
   const uint32_t np = NP > 0 ? (uint32_t)NP : np_rt;
@@ -155,14 +157,24 @@ __device__ __forceinline__ void sha512_private(const int32_t (&q)[kPixMaxPriv], 
     constexpr int t = decltype(tc)::value;
     sha512_round<t>(v, kSha512K[t] + W[t]);
   });
+  // schedule word t in place of word t - 16
+  auto extend = [&](auto rc) {
+    constexpr int r = decltype(rc)::value;
+    const uint64_t w15 = W[(r + 1) & 15], w2 = W[(r + 14) & 15];
+    const uint64_t s0 = xor3_64(rotr64<1>(w15), rotr64<8>(w15), w15 >> 7);
+    const uint64_t s1 = xor3_64(rotr64<19>(w2), rotr64<61>(w2), w2 >> 6);
+    W[r] += s0 + W[(r + 9) & 15] + s1;
+  };
+  static_for<0, 16>([&](auto rc) {
+    constexpr int r = decltype(rc)::value;
+    extend(rc);
+    sha512_round<r>(v, kSha512K[16 + r] + W[r]);
+  });
 #pragma unroll 1
-  for (uint32_t base = 16; base < 80; base += 16) {
+  for (uint32_t base = 32; base < 80; base += 16) {
     static_for<0, 16>([&](auto rc) {
       constexpr int r = decltype(rc)::value;
-      const uint64_t w15 = W[(r + 1) & 15], w2 = W[(r + 14) & 15];
-      const uint64_t s0 = xor3_64(rotr64<1>(w15), rotr64<8>(w15), w15 >> 7);
-      const uint64_t s1 = xor3_64(rotr64<19>(w2), rotr64<61>(w2), w2 >> 6);
-      W[r] += s0 + W[(r + 9) & 15] + s1;
+      extend(rc);
       sha512_round<r>(v, c_sha512.k[base + r] + W[r]);
     });
   }
