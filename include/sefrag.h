@@ -279,11 +279,12 @@ typedef struct sf_batch_item {
  * wavefront grabs tiles_per_grab consecutive tiles per atomic add.
  * schedule 1, static chunks: the tiles are cut into chunks of
  * 4 * tiles_per_grab consecutive tiles dealt round-robin to the workgroups,
- * the wavefronts of a workgroup taking every 4th tile of its chunk (faster on
- * large line-aligned images).  tiles_per_grab 0 = the schedule's default (8
- * queue, 2 static; at most 1024); workgroups_per_cu 0 = as many as fit.
- * reserved must be 0.  NULL tuning = {8, 0, 0, 0}.  Every shape gives the
- * same fragments. */
+ * the wavefronts of a workgroup taking every 4th tile of its chunk (faster
+ * but for very large batches).  tiles_per_grab 0 = the schedule's default (8
+ * queue, 1 static; at most 1024); workgroups_per_cu 0 = as many as fit.
+ * reserved must be 0.  NULL tuning = the library's choice by the number of
+ * tiles ({0, 0, 1, 0} up to 450 000 of them, else {0, 0, 0, 0}).  Every shape
+ * gives the same fragments. */
 typedef struct sf_batch_tuning {
   uint32_t tiles_per_grab;
   uint32_t workgroups_per_cu;

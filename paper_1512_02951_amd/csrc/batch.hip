@@ -10,19 +10,19 @@
 //                       (plain_tile.h) on every global tile, with the
 //                       geometry, selection, fragments and counter block of
 //                       the tile's image.  Two schedules:
-//                       work queue (default): a kernel clears a counter,
-//                       then each wave grabs tiles_per_grab consecutive
-//                       tiles per atomic.
-//                       static chunks: the global tiles are cut
-//                       into chunks of 4 * tiles_per_grab consecutive tiles,
-//                       dealt round-robin to the workgroups, the 4 waves of
-//                       a workgroup taking interleaved tiles of its chunk.
+//                       work queue (the default of very large plans): a
+//                       kernel clears a counter, then each wave grabs
+//                       tiles_per_grab consecutive tiles per atomic.
+//                       static chunks (the default of all others): the
+//                       global tiles are cut into chunks of
+//                       4 * tiles_per_grab consecutive tiles, dealt
+//                       round-robin to the workgroups, the 4 waves of a
+//                       workgroup taking interleaved tiles of its chunk.
 //                       The tiles in flight form one dense window, as in the
-//                       single-image kernels.  Faster on large line-aligned
-//                       images (the queue's waves work through their grabs
-//                       one tile after another, so the tiles in flight are
-//                       spread out), slower on the batching workload's many
-//                       unaligned ones.
+//                       single-image kernels; the queue's waves work through
+//                       their grabs one tile after another, so its tiles in
+//                       flight are spread out, a small plan's few grabs leave
+//                       most waves idle, and its counter needs a launch.
 //
 // The tuner times candidate (schedule, tiles_per_grab, workgroups per CU)
 // triples on the planned batch and reports the fastest.
@@ -117,7 +117,13 @@ __device__ __forceinline__ uint32_t find_image(const uint32_t *offs, const uint3
 }
 
 constexpr int kSchedQueue = 0, kSchedStatic = 1;
-constexpr uint32_t kDefaultChunkTiles = 2;
+constexpr uint32_t kDefaultChunkTiles = 1;
+// The schedule without a tuning argument: static chunks of one tile per wave
+// up to this many tiles, else the queue, 8 tiles per grab.  Round trips,
+// static 1 / queue 8 in us: 373 tiles 21 / 113, 5 912 58 / 130, 41 267
+// 317 / 436, 122 531 982 / 1 101, 31 785 of line-aligned images 256 / 359;
+// 444 168 tiles 3 672 / 3 669, 821 489 6 845 / 6 620.
+constexpr uint64_t kStaticMaxTiles = 450000;
 
 // Runs body(tile, desc) for every tile of the batch, in the schedule kSched
 // (see the top of this file).
@@ -299,10 +305,10 @@ int launch_batch(const DeviceState &ds, const PlanInfo &p, int which, const sf_b
   BatchArgs a;
   a.ws = (uint8_t *)p.ws;
   a.n = p.n;
-  const uint32_t sched = tuning ? tuning->schedule : (uint32_t)kSchedQueue;
+  const uint32_t sched = tuning ? tuning->schedule
+                                : (uint32_t)(p.total_tiles <= kStaticMaxTiles ? kSchedStatic : kSchedQueue);
   if ((sched != (uint32_t)kSchedStatic && sched != (uint32_t)kSchedQueue) || (tuning && tuning->reserved))
     return fail(SF_EINVAL, "schedule must be 0 (work queue) or 1 (static chunks), reserved 0");
-  // defaults: what the tuner picks on the batching workload
   a.tiles_per_grab = tuning && tuning->tiles_per_grab ? tuning->tiles_per_grab
                                                       : (sched == (uint32_t)kSchedStatic ? kDefaultChunkTiles : 8u);
   a.lds_priv_bytes = (2u * p.max_npriv * 64u + 15u) & ~15u;
