@@ -265,18 +265,45 @@ __global__ __launch_bounds__(kThreads) void sm_stats_kernel(SmArgs a) {
   wg_partials<kCorrStats, 0>(0.0f, acc, a.partials, g);
 }
 
-__global__ __launch_bounds__(kThreads) void sm_backward_kernel(SmArgs a) {
+// The next tile's x is loaded as soon as the current tile's products begin to
+// be reduced (2 waves per SIMD, 256 registers each), so it is in flight during
+// the reduction; G follows at its place in the next tile.
+__global__ __launch_bounds__(kThreads, 2) void sm_backward_kernel(SmArgs a) {
   const SmGeom &g = a.g;
   const size_t plane = (size_t)blockIdx.y * g.H * g.W;
+  const int lane = threadIdx.x & 63;
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t stride = gridDim.x * kWaves;
+  uint32_t t = blockIdx.x * kWaves + wave;
+  auto origin = [&](uint32_t tile, bool &valid) -> uint32_t {
+    const uint32_t blk = tile * 64u + (uint32_t)lane;
+    valid = blk < g.blocks;
+    const uint32_t by = blk / g.Bx, bx = blk - by * g.Bx;
+    return valid ? by * 8u * g.W + bx * 8u : 0u;
+  };
   float acc = 0.0f;  // lane n: sum of DCT(G)_n DCT(x)_n over the wave's blocks
-  sm_tiles(g, [&](uint32_t org, bool valid) {
-    float cx[64], cg[64];
+  float cx[64];
+  bool valid = false;
+  uint32_t org = 0;
+  if (t < g.tiles) {
+    org = origin(t, valid);
     load_fblock(a.x + plane, g.W, org, valid, cx);
-    fdct8x8(cx, a.K);
+  }
+  while (t < g.tiles) {
+    float cg[64];
     load_fblock(a.y + plane, g.W, org, valid, cg);
+    fdct8x8(cx, a.K);
     fdct8x8(cg, a.K);  // adjoint of the inverse transform
-    acc += wave_reduce_scatter([&](int n) { return cg[n] * cx[n]; });
-  });
+#pragma unroll
+    for (int n = 0; n < 64; ++n) cg[n] *= cx[n];
+    __builtin_amdgcn_sched_barrier(0);
+    t += stride;
+    if (t < g.tiles) {
+      org = origin(t, valid);
+      load_fblock(a.x + plane, g.W, org, valid, cx);
+    }
+    acc += wave_reduce_scatter([&](int n) { return cg[n]; });
+  }
   wg_partials<64, 64>(acc, nullptr, a.partials, g);
 }
 
@@ -656,10 +683,13 @@ __global__ void sm_corr_grad_kernel(const float *x, const float *p, const float 
 }
 
 // dL/dl_n = sigmoid'(l_n) * dL/dm_n with dL/dm_n = -sum DCT(G)_n DCT(x)_n.
+__device__ __forceinline__ float adjoint_grad(double sum, float logit) {
+  const double m = 1.0 / (1.0 + exp(-(double)logit));
+  return (float)(m * (1.0 - m) * -sum);
+}
+
 __global__ void sm_adjoint_grad_kernel(const double *adj, const float *logits, float *grad_logits) {
-  const int n = threadIdx.x;
-  const double m = 1.0 / (1.0 + exp(-(double)logits[n]));
-  grad_logits[n] = (float)(m * (1.0 - m) * -adj[n]);
+  grad_logits[threadIdx.x] = adjoint_grad(adj[threadIdx.x], logits[threadIdx.x]);
 }
 
 int sm_check(uint32_t B, uint32_t H, uint32_t W) {
@@ -670,8 +700,10 @@ int sm_check(uint32_t B, uint32_t H, uint32_t W) {
 
 // Many parts per output: one workgroup per output, 256 threads summing
 // strided parts in a fixed order, then a fixed LDS tree (deterministic).
+// With logits given (one item, kN = 64), out is not written but
+// grad_logits[n] = sigmoid'(l_n) * -sum: the adjoint's dL/dl in the same launch.
 __global__ __launch_bounds__(256) void sm_reduce_wide_kernel(const double *partials, uint32_t parts, uint32_t kN,
-                                                              double *out) {
+                                                              double *out, const float *logits, float *grad_logits) {
   __shared__ double s[256];
   const uint32_t o = blockIdx.x, i = o / kN, k = o - i * kN;
   double v = 0.0;
@@ -682,14 +714,20 @@ __global__ __launch_bounds__(256) void sm_reduce_wide_kernel(const double *parti
     if (threadIdx.x < w) s[threadIdx.x] += s[threadIdx.x + w];
     __syncthreads();
   }
-  if (threadIdx.x == 0) out[o] = s[0];
+  if (threadIdx.x == 0) {
+    if (logits) grad_logits[o] = adjoint_grad(s[0], logits[o]);
+    else out[o] = s[0];
+  }
 }
 
+bool reduce_wide(uint32_t parts) { return parts > 64; }
+
 int sm_launch_reduce(const double *partials, uint32_t items, uint32_t parts, uint32_t kN, double *out,
-                     hipStream_t stream) {
+                     hipStream_t stream, const float *logits = nullptr, float *grad_logits = nullptr) {
   const uint32_t total = items * kN;
-  if (parts > 64)
-    hipLaunchKernelGGL(sm_reduce_wide_kernel, dim3(total), dim3(256), 0, stream, partials, parts, kN, out);
+  if (reduce_wide(parts))
+    hipLaunchKernelGGL(sm_reduce_wide_kernel, dim3(total), dim3(256), 0, stream, partials, parts, kN, out, logits,
+                       grad_logits);
   else
     hipLaunchKernelGGL(sm_reduce_kernel, dim3((total + 255) / 256), dim3(256), 0, stream, partials, items, parts,
                        kN, out);
@@ -783,8 +821,10 @@ int softmask_backward(const DeviceState &ds, const float *x, const float *gpub, 
   hipLaunchKernelGGL(sm_backward_kernel, dim3(g.wg_per_image, B), dim3(kThreads), 0, stream, a);
   // all images and workgroups together: one item of B * wg_per_image parts
   double *adj = (double *)((uint8_t *)ws + (size_t)B * g.wg_per_image * kStats * sizeof(double));
-  sm_launch_reduce(a.partials, 1, B * g.wg_per_image, 64, adj, stream);
-  hipLaunchKernelGGL(sm_adjoint_grad_kernel, dim3(1), dim3(64), 0, stream, adj, logits, grad_logits);
+  const uint32_t parts = B * g.wg_per_image;
+  sm_launch_reduce(a.partials, 1, parts, 64, adj, stream, logits, grad_logits);
+  if (!reduce_wide(parts))
+    hipLaunchKernelGGL(sm_adjoint_grad_kernel, dim3(1), dim3(64), 0, stream, adj, logits, grad_logits);
   hipError_t e = hipGetLastError();
   return e == hipSuccess ? SF_OK : hip_fail(e, "soft-mask backward launch");
 }
