@@ -112,14 +112,30 @@ def aes_ctr(key: bytes | None, ctr0: bytes | None):
     return SfAesCtr.from_buffer_copy(k + c)
 
 
-# Pure functions of their arguments that every call needs: computed once per
-# image shape and selection in use (a small call's time is mostly host work).
-@functools.lru_cache(maxsize=256, typed=True)
+_PLAIN = frozenset((int, bool, str))
+
+
+def by_value(f):
+    """Keep a pure function's results by its positional arguments (a small call's
+    time is mostly host work, and every call needs the same few sizes).  Only
+    plain numbers and strings are keys: other types that the library takes
+    (0-d arrays, tensors) may be unhashable, or change under one identity, and
+    are computed each time."""
+    kept = functools.lru_cache(maxsize=256, typed=True)(f)
+
+    @functools.wraps(f)
+    def call(*args):
+        return kept(*args) if _PLAIN.issuperset(map(type, args)) else f(*args)
+
+    return call
+
+
+@by_value
 def _desc(H: int, W: int, C: int, mask: int, precision) -> SfDesc:
     return desc(H, W, C, mask, precision)
 
 
-@functools.lru_cache(maxsize=256, typed=True)
+@by_value
 def _fragment_sizes(H: int, W: int, C: int, mask: int, precision):
     d = desc(H, W, C, mask, precision)
     pb, qb, rb = ctypes.c_size_t(), ctypes.c_size_t(), ctypes.c_size_t()
@@ -127,7 +143,7 @@ def _fragment_sizes(H: int, W: int, C: int, mask: int, precision):
     return pb.value, qb.value, rb.value
 
 
-@functools.lru_cache(maxsize=256, typed=True)
+@by_value
 def _exception_bytes(H: int, W: int, C: int, mask: int, per_tile: int, precision):
     d = desc(H, W, C, mask, precision)
     nbytes, needed = ctypes.c_size_t(), ctypes.c_int()

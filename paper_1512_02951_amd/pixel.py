@@ -5,10 +5,9 @@ run in the HIP library."""
 from __future__ import annotations
 
 import ctypes
-import functools
 from dataclasses import dataclass
 
-from . import SfAesCtr, SfDesc, aes_ctr, check, desc, lib as _base_lib, _stream
+from . import SfAesCtr, SfDesc, aes_ctr, by_value, check, desc, lib as _base_lib, _stream
 
 SF_LEVEL_FIRST, SF_LEVEL_STRONG, SF_STORAGE_8BIT = 0, 1, 2
 
@@ -45,7 +44,7 @@ def fragment_sizes(H: int, W: int, C: int, mask: int, strong: bool = False, stor
     return _fragment_sizes(H, W, C, mask, strong, storage_bits)
 
 
-@functools.lru_cache(maxsize=256, typed=True)
+@by_value
 def _fragment_sizes(H, W, C, mask, strong, storage_bits):
     d = desc(H, W, C, mask)
     pb, qb = ctypes.c_size_t(), ctypes.c_size_t()
