@@ -421,10 +421,15 @@ int pixel_defrag_image(const sf_desc *desc, int flags, const uint8_t *d_public, 
  *     blocks of Eq. (3) over the block's 64 samples (h = 8, at most 6).
  * d_block_entropy (optional, NULL to skip): 2 * C * (H/8) * (W/8) floats,
  * the block entropies of X then of Y, block order of frag_image.
- * d_ws: caller-owned device workspace of sf_stats_workspace_bytes() bytes,
- * 16-byte aligned; its first 65536 uint32 hold the joint histogram
- * (bin 256 x + y) after the call.  X and Y 16-byte aligned.  Errors:
- * SF_EINVAL (NULL, misaligned, workspace too small), SF_ESHAPE, SF_EHIP.
+ * d_ws: caller-owned device workspace, 16-byte aligned; its first 65536
+ * uint32 hold the joint histogram (bin 256 x + y) after the call.
+ * sf_stats_workspace_bytes() (about 17 MB) serves every image: the joint
+ * histogram is counted in up to 256 parts of 64 KB.  A smaller workspace, down
+ * to 629088 bytes, gives the same results; if it has no room for the image's
+ * parts (one per 32768 samples, at least one), they are summed by atomics
+ * instead, which takes longer.
+ * X and Y 16-byte aligned.  Errors: SF_EINVAL (NULL, misaligned, workspace
+ * below 629088 bytes), SF_ESHAPE, SF_EHIP.
  * ------------------------------------------------------------------- */
 typedef struct sf_security_stats {
   uint64_t samples;

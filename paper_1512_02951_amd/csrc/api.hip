@@ -580,11 +580,11 @@ int sf_security_stats_compute(const uint8_t *d_x, const uint8_t *d_y, uint32_t H
   if ((uint64_t)H * W * C >= (1ull << 32)) return fail(SF_ESHAPE, "image must hold fewer than 2^32 samples");
   if (((uintptr_t)d_x | (uintptr_t)d_y | (uintptr_t)d_ws) & 15u) return fail(SF_EINVAL, "buffers must be 16-byte aligned");
   if (((uintptr_t)d_out & 7u) || ((uintptr_t)d_block_entropy & 3u)) return fail(SF_EINVAL, "misaligned output");
-  if (ws_bytes < stats_workspace_bytes()) return fail(SF_EINVAL, "workspace too small");
+  if (ws_bytes < stats_least_workspace_bytes()) return fail(SF_EINVAL, "workspace too small");
   DeviceState *ds;
   int rc = device_state(&ds);
   if (rc) return rc;
-  rc = launch_security_stats(*ds, d_x, d_y, H, W, C, d_ws, d_out, d_block_entropy, (hipStream_t)stream);
+  rc = launch_security_stats(*ds, d_x, d_y, H, W, C, d_ws, ws_bytes, d_out, d_block_entropy, (hipStream_t)stream);
   if (rc == SF_OK) t_last_error.clear();
   return rc;
 }

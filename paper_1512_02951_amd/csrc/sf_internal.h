@@ -174,9 +174,11 @@ int launch_pixel_defrag(const DeviceState &ds, const Geom &g, int flags, const u
                         const AesArgs &aes, uint8_t *pix, hipStream_t stream);
 
 // Security statistics (stats.hip).
-size_t stats_workspace_bytes();
+size_t stats_workspace_bytes();        // what any image can use
+size_t stats_least_workspace_bytes();  // what every image needs
 int launch_security_stats(const DeviceState &ds, const uint8_t *x, const uint8_t *y, uint32_t H, uint32_t W,
-                          uint32_t C, void *ws, sf_security_stats *out, float *block_entropy, hipStream_t stream);
+                          uint32_t C, void *ws, size_t ws_bytes, sf_security_stats *out, float *block_entropy,
+                          hipStream_t stream);
 
 // Differentiation form (softmask.hip).
 size_t softmask_workspace_bytes(const DeviceState &ds, uint32_t B, uint32_t H, uint32_t W);

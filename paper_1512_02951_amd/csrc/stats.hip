@@ -412,7 +412,8 @@ struct JointArgs {
   uint64_t nvec;       // samples / 16
   uint64_t per_chunk;  // vectors per workgroup
   uint32_t *hist;      // 65536 bins, bin = 256 x + y: the counts' parts above 255
-  uint8_t *bytes;      // per workgroup, the low bytes of its 65536 counts
+  uint8_t *bytes;      // per workgroup, the low bytes of its 65536 counts; or
+                       // NULL: no room for them, hist gets whole counts
 };
 
 // Counts of both samples of p (bins 256 x + y in its halves).
@@ -472,6 +473,14 @@ __global__ __launch_bounds__(kJointThreads) void stats_joint_kernel(JointArgs a)
     }
   }
   __syncthreads();
+  if (!a.bytes) {
+    for (uint32_t i = threadIdx.x; i < kHalfBins; i += kJointThreads) {
+      const uint32_t c = s_bins[i];
+      if (c & 0xffffu) atomicAdd(&a.hist[i], c & 0xffffu);
+      if (c >> 16) atomicAdd(&a.hist[kHalfBins + i], c >> 16);
+    }
+    return;
+  }
   uint32_t *out = reinterpret_cast<uint32_t *>(a.bytes + (size_t)blockIdx.x * 2u * kHalfBins);
   for (uint32_t i = threadIdx.x; i < kHalfBins / 4u; i += kJointThreads) {
     const uint4 c = reinterpret_cast<const uint4 *>(s_bins)[i];
@@ -731,10 +740,12 @@ static_assert(kHistBytes % 16 == 0 && kPartBytes % 16 == 0, "workspace parts sta
 
 static_assert(sizeof(Reduced) % 16 == 0, "workspace parts stay 16-byte aligned");
 
-size_t stats_workspace_bytes() { return kHistBytes + kPartBytes + sizeof(Reduced) + kJointGrid * 2u * kHalfBins; }
+size_t stats_least_workspace_bytes() { return kHistBytes + kPartBytes + sizeof(Reduced); }
+size_t stats_workspace_bytes() { return stats_least_workspace_bytes() + kJointGrid * 2u * kHalfBins; }
 
 int launch_security_stats(const DeviceState &ds, const uint8_t *x, const uint8_t *y, uint32_t H, uint32_t W,
-                          uint32_t C, void *ws, sf_security_stats *out, float *block_entropy, hipStream_t stream) {
+                          uint32_t C, void *ws, size_t ws_bytes, sf_security_stats *out, float *block_entropy,
+                          hipStream_t stream) {
   const StatsGeom g = stats_geom(H, W, C);
   uint32_t *hist = static_cast<uint32_t *>(ws);
   Partial *parts = reinterpret_cast<Partial *>(static_cast<uint8_t *>(ws) + kHistBytes);
@@ -763,9 +774,13 @@ int launch_security_stats(const DeviceState &ds, const uint8_t *x, const uint8_t
   const uint64_t chunks = std::max<uint64_t>(1, std::min<uint64_t>(std::min<uint64_t>((uint64_t)ds.num_cu, kJointGrid), j.nvec / 2048u));
   j.per_chunk = (j.nvec + chunks - 1) / chunks;
   j.hist = hist;
-  j.bytes = bytes;
+  // a workspace without room for every joint workgroup's counts (sized for
+  // the least, which is what it took before there were any) still serves: the
+  // joint histogram is then summed by atomics
+  const bool room = ws_bytes >= stats_least_workspace_bytes() + chunks * 2u * kHalfBins;
+  j.bytes = room ? bytes : nullptr;
   hipLaunchKernelGGL(stats_joint_kernel, dim3((uint32_t)chunks), dim3(kJointThreads), 0, stream, j);
-  FinArgs f{g, parts, grid, hist, bytes, (uint32_t)chunks, red, out};
+  FinArgs f{g, parts, grid, hist, bytes, room ? (uint32_t)chunks : 0u, red, out};
   hipLaunchKernelGGL(stats_rows_kernel, dim3(256), dim3(kFinThreads), 0, stream, f);
   hipLaunchKernelGGL(stats_finalize_kernel, dim3(1), dim3(kFinThreads), 0, stream, f);
   hipError_t e = hipGetLastError();

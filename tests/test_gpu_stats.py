@@ -128,6 +128,39 @@ def test_joint_counts_above_a_byte_and_between_parts(shape, values):
     assert got["hist_x"] == ref.sum(1).tolist() and got["hist_y"] == ref.sum(0).tolist()
 
 
+LEAST_WORKSPACE = 629088  # documented in sefrag.h: histogram, partial moments, sums
+
+
+@pytest.mark.parametrize("shape", [(1, 64, 72), (1, 1024, 1024), (3, 1080, 1920)])
+@pytest.mark.parametrize("parts", [0, 1, 31, 32, 256])
+def test_smaller_workspaces_are_accepted(shape, parts):
+    # from the size without any part's counts on, on both sides of the image's
+    # number of parts (1, 32 and 189); the record is the same byte for byte, and
+    # nothing is written past the size given
+    g = torch.Generator().manual_seed(7)
+    x = torch.randint(0, 256, shape, dtype=torch.uint8, generator=g).cuda()
+    y = torch.randint(0, 40, shape, dtype=torch.uint8, generator=g).cuda()
+    full = stats.StatsRunner(x.device)
+    full.launch(x, y)
+    r = stats.StatsRunner(x.device)
+    n = LEAST_WORKSPACE + 65536 * parts
+    guard = torch.full((n + 65536,), 0xA5, dtype=torch.uint8, device="cuda")
+    r.ws = guard[:n]
+    r.launch(x, y)
+    assert torch.equal(r.out, full.out)
+    assert torch.equal(r.joint_histogram(), full.joint_histogram())
+    assert bool((guard[n:] == 0xA5).all())
+
+
+def test_workspace_below_the_least_size_is_refused():
+    x = torch.zeros((1, 8, 8), dtype=torch.uint8, device="cuda")
+    r = stats.StatsRunner(x.device)
+    r.ws = r.ws[:LEAST_WORKSPACE - 1]
+    with pytest.raises(sf.SefragError) as e:
+        r.launch(x, x)
+    assert e.value.code == sf.SF_EINVAL
+
+
 def test_tall_narrow_image_sums_stay_exact():
     # W = 8: one lane pair per band, 2^24 bands (4096 per wave): far more than
     # a 32-bit lane sum of squares could hold without the periodic flush.
