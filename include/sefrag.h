@@ -283,8 +283,9 @@ typedef struct sf_batch_item {
  * but for very large batches).  tiles_per_grab 0 = the schedule's default (8
  * queue, 1 static; at most 1024); workgroups_per_cu 0 = as many as fit.
  * reserved must be 0.  NULL tuning = the library's choice by the number of
- * tiles ({0, 0, 1, 0} up to 450 000 of them, else {0, 0, 0, 0}).  Every shape
- * gives the same fragments. */
+ * tiles: {0, 0, 1, 0} up to 450 000 of them, else {0, 0, 0, 0}; for frag, if the
+ * plan holds other selections than DC + 1, 2, 5 or 9 AC, up to 90 000, or 40 000
+ * if one of them has more than 16 AC.  Every shape gives the same fragments. */
 typedef struct sf_batch_tuning {
   uint32_t tiles_per_grab;
   uint32_t workgroups_per_cu;

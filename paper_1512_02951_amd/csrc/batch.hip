@@ -119,11 +119,20 @@ __device__ __forceinline__ uint32_t find_image(const uint32_t *offs, const uint3
 constexpr int kSchedQueue = 0, kSchedStatic = 1;
 constexpr uint32_t kDefaultChunkTiles = 1;
 // The schedule without a tuning argument: static chunks of one tile per wave
-// up to this many tiles, else the queue, 8 tiles per grab.  Round trips,
-// static 1 / queue 8 in us: 373 tiles 21 / 113, 5 912 58 / 130, 41 267
-// 317 / 436, 122 531 982 / 1 101, 31 785 of line-aligned images 256 / 359;
-// 444 168 tiles 3 672 / 3 669, 821 489 6 845 / 6 620.
+// up to this many tiles, else the queue, 8 tiles per grab.  Round trips of
+// compiled selections, static 1 / queue 8 in us: 373 tiles 21 / 113, 5 912
+// 58 / 130, 41 267 317 / 436, 122 531 982 / 1 101, 31 785 of line-aligned images
+// 256 / 359; 444 168 tiles 3 672 / 3 669, 821 489 6 845 / 6 620.
 constexpr uint64_t kStaticMaxTiles = 450000;
+// frag of plans with selections known at run time: there the queue wins
+// earlier, the more so with more than 16 private AC coefficients (the vector
+// quantiser).  frag, static 1 / queue 8 in us, at most 16 AC: 47 544 tiles 273 /
+// 319, 71 880 415 / 436, 83 428 475 / 485, 122 531 680 / 660, 318 165 1 726 /
+// 1 527; beyond 16 AC in some image: 13 901 144-187 / 207-217, 38 723 314-478 /
+// 345-472, 44 786 465-558 / 413-579, 83 428 774-1 032 / 655-950, 318 165 2 760 /
+// 2 241.  defrag has no such body: static 1 / queue 8 at 122 531 tiles 478-763 /
+// 559-777.
+constexpr uint64_t kStaticMaxTilesByRank = 90000, kStaticMaxTilesVector = 40000;
 
 // Runs body(tile, desc) for every tile of the batch, in the schedule kSched
 // (see the top of this file).
@@ -286,6 +295,7 @@ struct PlanInfo {
   bool all_pixels = true;    // every item has d_pixels: frag can run
   bool all_restored = true;  // every item has d_restored: defrag can run
   bool any_mask = false;     // some item's selection has no compiled body
+  bool any_vector = false;   // some item's needs the vector quantiser (over kQ2MfmaMaxAc AC)
 };
 std::vector<PlanInfo> g_plans;  // guarded by g_plan_mu
 std::mutex g_plan_mu;
@@ -300,13 +310,18 @@ int find_plan(const void *ws, PlanInfo *out) {
   return fail(SF_EINVAL, "workspace has no batch plan (call sf_batch_plan first)");
 }
 
+uint64_t static_max_tiles(const PlanInfo &p, int which) {
+  if (which != 0 || !p.any_mask) return kStaticMaxTiles;
+  return p.any_vector ? kStaticMaxTilesVector : kStaticMaxTilesByRank;
+}
+
 int launch_batch(const DeviceState &ds, const PlanInfo &p, int which, const sf_batch_tuning *tuning,
                  uint32_t *status, hipStream_t stream) {
   BatchArgs a;
   a.ws = (uint8_t *)p.ws;
   a.n = p.n;
   const uint32_t sched = tuning ? tuning->schedule
-                                : (uint32_t)(p.total_tiles <= kStaticMaxTiles ? kSchedStatic : kSchedQueue);
+                                : (uint32_t)(p.total_tiles <= static_max_tiles(p, which) ? kSchedStatic : kSchedQueue);
   if ((sched != (uint32_t)kSchedStatic && sched != (uint32_t)kSchedQueue) || (tuning && tuning->reserved))
     return fail(SF_EINVAL, "schedule must be 0 (work queue) or 1 (static chunks), reserved 0");
   a.tiles_per_grab = tuning && tuning->tiles_per_grab ? tuning->tiles_per_grab
@@ -361,7 +376,7 @@ int batch_plan(const DeviceState &ds, const sf_batch_item *items, uint32_t n, co
   if (key) aes_expand_key(key, hd->key.rk);
   uint64_t total = 0;
   uint32_t max_npriv = 1;
-  bool all_pixels = true, all_restored = true, any_mask = false;
+  bool all_pixels = true, all_restored = true, any_mask = false, any_vector = false;
   for (uint32_t i = 0; i < n; ++i) {
     const sf_batch_item &it = items[i];
     sf_desc d;
@@ -398,6 +413,7 @@ int batch_plan(const DeviceState &ds, const sf_batch_item *items, uint32_t n, co
     bd.ctr_hi = hi;
     bd.ctr_lo = lo;
     any_mask = any_mask || !compiled_mask(g.mask);
+    any_vector = any_vector || __builtin_popcountll(g.mask & ~1ull) > kQ2MfmaMaxAc;
     offs[i] = (uint32_t)total;
     total += g.ntiles;
     if (total >= (1ull << 31)) return fail(SF_ERANGE, "batch holds too many tiles");
@@ -430,6 +446,7 @@ int batch_plan(const DeviceState &ds, const sf_batch_item *items, uint32_t n, co
   p.all_pixels = all_pixels;
   p.all_restored = all_restored;
   p.any_mask = any_mask;
+  p.any_vector = any_vector;
   std::lock_guard<std::mutex> lk(g_plan_mu);
   for (PlanInfo &q : g_plans)
     if (q.ws == d_ws) {

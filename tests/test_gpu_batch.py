@@ -86,6 +86,62 @@ def test_tunings_give_identical_results(tuning):
     _check_against_single(b, imgs, masks, ctrs, key)
 
 
+def _run_time_masks(n, seed):
+    """Selections without a compiled body for the matrix-core quantiser, 1 to 16
+    private AC with and without DC, alternating with compiled ones, images of
+    one selection after the other and back."""
+    rng = np.random.default_rng(seed)
+    imgs, masks, ctrs = [], [], []
+    for i in range(n):
+        H, W = int(8 * rng.integers(1, 30)), int(8 * rng.integers(1, 50))
+        imgs.append(synth.image(H, W, int(rng.choice([1, 3])), 4, 3000 + i).cuda())
+        ac = 1 + i % 16
+        m = sum(1 << int(z) for z in rng.choice(np.arange(1, 64), ac, replace=False)) | (i // 3) % 2
+        masks.append(m if i % 4 else sf.prefix_mask((1, 2, 5, 9)[i // 4 % 4]))
+        ctrs.append(synth.ctr0(4, 3000 + i))
+    masks[n - 1] = masks[1]
+    return imgs, masks, ctrs
+
+
+@pytest.mark.parametrize("wide", [False, True])
+@pytest.mark.parametrize("tuning", [None, (1, 0, 0), (8, 0, 0), (1, 0, 1), (4, 1, 1)])
+def test_run_time_selections_by_rank(tuning, wide):
+    # wide: one selection of 17 AC, so that both quantisers serve the plan
+    imgs, masks, ctrs = _run_time_masks(36, 9)
+    if wide:
+        masks[5] = sum(1 << z for z in range(2, 36, 2))
+        assert bin(masks[5]).count("1") == 17
+    key = synth.aes_key(4)
+    b = Batch(imgs, masks, key, ctrs)
+    status = torch.zeros(1, dtype=torch.int32, device="cuda")
+    b.frag(tuning, status=status)
+    b.defrag(tuning, status=status)
+    torch.cuda.synchronize()
+    assert int(status.item()) == 0
+    _check_against_single(b, imgs, masks, ctrs, key)
+    for i in range(0, len(imgs), 5):  # oracle directly
+        ref = oracle.frag(imgs[i].cpu().numpy(), masks[i], key, ctrs[i])
+        assert np.array_equal(b.privates[i].cpu().numpy()[: ref["cipher"].size], ref["cipher"])
+
+
+# tiles at the default schedules' lines: selections compiled (static below and
+# above), by rank (90 000) and with the vector quantiser (40 000)
+@pytest.mark.parametrize("tiles", [40000, 40001, 90000, 90001])
+@pytest.mark.parametrize("masks", [(0x3F, 0x7), (0x9F, 0x3F), (0x9F, 0xFFFFF0)])
+def test_default_schedules_at_their_lines(tiles, masks):
+    # images of one tile of 64 blocks a row of 512 samples: H / 8 tiles each
+    sizes = [(8 * (tiles // 2), 512), (8 * (tiles - tiles // 2), 512)]
+    imgs = [torch.randint(0, 256, (1, h, w), dtype=torch.uint8, device="cuda",
+                          generator=torch.Generator("cuda").manual_seed(tiles + i)) for i, (h, w) in enumerate(sizes)]
+    ctrs = [synth.ctr0(4, 4000 + i) for i in range(2)]
+    key = synth.aes_key(4)
+    b = Batch(imgs, masks, key, ctrs)
+    b.frag()
+    b.defrag()
+    torch.cuda.synchronize()
+    _check_against_single(b, imgs, masks, ctrs, key)
+
+
 def test_graph_replays_and_autotune(tmp_path):
     imgs, masks, ctrs = _mixed(16, 6)
     key = synth.aes_key(4)
