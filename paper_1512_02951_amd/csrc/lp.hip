@@ -449,16 +449,17 @@ __device__ __forceinline__ void group_ctr(const TileGroup &G, const WaveLds &W, 
   if (nrow != total) group_ctr_tail<kEncrypt>(G, W, pstride, gpriv, npriv, lane, s_aes, aes, nrow, n0, total);
 }
 
-// The eight row words (columns 4h .. 4h + 3) of the lane's block in one half;
-// img spans the whole image (fewer than 2^32 samples), rows are W apart.
-// Lanes without a block take an offset beyond it, which loads zero.
+// The eight row words (columns 4h .. 4h + 3) of the lane's block in one half,
+// zero without a block; img spans the whole image (fewer than 2^32 samples),
+// rows are W apart.
 __device__ __forceinline__ void load_rows(const TileGeom &g, __amdgpu_buffer_rsrc_t img, uint32_t t, uint32_t nt,
-                                          uint32_t (&xr)[8]) {
-  const uint32_t lane = fresh_lane();
-  const uint64_t b = (uint64_t)t * 64u + 32u * nt + (lane & 31u);
-  const uint32_t voff = b < g.nb ? block_origin(g, (uint32_t)b) + 4u * (lane >> 5) : 0xfffffff0u;
+                                          int lane, uint32_t (&xr)[8]) {
+  const uint64_t b = (uint64_t)t * 64u + 32u * nt + ((uint32_t)lane & 31u);
+  const bool valid = b < g.nb;
+  const uint32_t voff = valid ? block_origin(g, (uint32_t)b) + 4u * (fresh_lane() >> 5) : 0u;
 #pragma unroll
-  for (int r = 0; r < 8; ++r) xr[r] = __builtin_amdgcn_raw_buffer_load_b32(img, voff, (int)(r * g.W), kNonTemporal);
+  for (int r = 0; r < 8; ++r)
+    xr[r] = valid ? __builtin_amdgcn_raw_buffer_load_b32(img, voff, (int)(r * g.W), kNonTemporal) : 0u;
 }
 
 // The one reconstruction routine: y[mt] (rows 4 mt .. 4 mt + 3 of the lane's
@@ -589,8 +590,7 @@ __device__ __forceinline__ void stage_repack(uint8_t *stage, uint32_t npriv, uin
 // ---------------------------------------------------------------------------
 // frag
 // Register budget: 4 waves per SIMD (128 VGPRs) for both storage types
-// (bf16 frag spills 2 registers there and still runs 7-8 % faster than at
-// 3 waves per SIMD with 138 VGPRs).
+// (nothing spilled).
 template <bool BF>
 constexpr int lp_waves_per_eu() {
   return 4;
@@ -609,24 +609,33 @@ __global__ __launch_bounds__(512, lp_waves_per_eu<BF>()) void lp_frag_kernel(LpA
   RunSel rs{0u, 0u};
   if constexpr (!MP::kStatic) rs = run_sel(g.mask, lane, wave == 0u, s_rank[0]);
   LpQ2 *s_q2 = reinterpret_cast<LpQ2 *>(s_dyn + kRankBytes<MP>);
-  // the tables' loads, then the first half's pixels, then the waits for the
-  // tables only (see AesFill)
+  // every table's loads (of the quantiser operands a thread's first), then the
+  // first half's pixels, then the waits for the tables only (see AesFill).  The
+  // operands' loads must not follow the pixels': waits are in order, so the
+  // tables were then complete after the pixels only, and with no cipher or few
+  // private positions frag was slower than with all of it in sequence (1080 x
+  // 1920 RGB fp16, us: DC + 1 AC 13.7 in sequence, 14.7 so, 13.9 now; DC + 5 AC
+  // without a cipher 12.5, 13.3, 12.7; DC + 9 AC 16.2, 16.1, 15.4).
   uint32_t t = blockIdx.x * nw + wave;
   const __amdgpu_buffer_rsrc_t img = buffer_rsrc(g.pix, (uint32_t)(g.nb * 64u));
+  auto q2_operand = [&](uint32_t i) {
+    const uint32_t rank = 16u * (i >> 6) + (i & 15u);
+    const int z = rank < g.npriv ? (int)((a.plist[rank >> 2] >> (8u * (rank & 3u))) & 0xffu) : -1;
+    return lp_q2_operand(a.q2, z, (int)(i & 63u));
+  };
+  const uint32_t nq2 = 64u * a.npass;
   AesFill fill;
   LpTableFill<BF> tabs;
   fill.load(a.aes_t0, a.aes.key, threadIdx.x);
   tabs.load(a.tables, threadIdx.x);
+  const LpQ2 q2first = q2_operand(min(threadIdx.x, nq2 - 1u));
   uint32_t xn[8];  // the next half's pixel rows, in flight during the current half
-  load_rows(g, img, t, 0, xn);
+  load_rows(g, img, t, 0, lane, xn);
   __builtin_amdgcn_sched_barrier(0);
   if (wave == 0u) fill.store(s_aes, threadIdx.x);
   tabs.store(s_tab, a.tables, threadIdx.x, blockDim.x);
-  for (uint32_t i = threadIdx.x; i < 64u * a.npass; i += blockDim.x) {
-    const uint32_t rank = 16u * (i >> 6) + (i & 15u);
-    const int z = rank < g.npriv ? (int)((a.plist[rank >> 2] >> (8u * (rank & 3u))) & 0xffu) : -1;
-    s_q2[i] = lp_q2_operand(a.q2, z, (int)(i & 63u));
-  }
+  if (threadIdx.x < nq2) s_q2[threadIdx.x] = q2first;
+  for (uint32_t i = threadIdx.x + blockDim.x; i < nq2; i += blockDim.x) s_q2[i] = q2_operand(i);
   __syncthreads();
   WaveLds W;
   W.priv = s_dyn + kRankBytes<MP> + 64u * a.npass * sizeof(LpQ2) + wave * a.wave_lds;
@@ -660,7 +669,8 @@ __global__ __launch_bounds__(512, lp_waves_per_eu<BF>()) void lp_frag_kernel(LpA
         uint32_t xr[8];
 #pragma unroll
         for (int r = 0; r < 8; ++r) xr[r] = xn[r];
-        load_rows(g, img, nt == 0 ? t : tn, nt ^ 1u, xn);  // zero, unread, past the last tile
+        if (nt == 0) load_rows(g, img, t, 1, lane, xn);
+        else if (tn < g.ntiles) load_rows(g, img, tn, 0, lane, xn);
 
         // ---- private integers (int8 matrix products), into the stage
         {
@@ -839,14 +849,14 @@ __global__ __launch_bounds__(512, lp_waves_per_eu<BF>()) void lp_frag_kernel(LpA
         uint16_t *pub_tile = a.pub + b0 * npub;
         if (ntb == 64u) {
           const __amdgpu_buffer_rsrc_t prs = buffer_rsrc(pub_tile, npub * 128u);
-          for (uint32_t c = fresh_lane(); c < 4u * npub; c += 64u) {
+          for (uint32_t c = (uint32_t)lane; c < 4u * npub; c += 64u) {
             const uint4 v = *reinterpret_cast<const uint4 *>(W.pub + 16u * c);
             const u32x4 vv = {v.x, v.y, v.z, v.w};
             __builtin_amdgcn_raw_buffer_store_b128(vv, prs, 64u * npub * nt + 16u * c, 0, kNonTemporal);
           }
         } else {
           const uint32_t m0 = min(32u, ntb), nv = ntb > 32u * nt ? min(32u, ntb - 32u * nt) : 0u;
-          for (uint32_t c = fresh_lane(); c < 32u * npub; c += 64u) {
+          for (uint32_t c = (uint32_t)lane; c < 32u * npub; c += 64u) {
             const uint32_t r = c >> 5, j = c & 31u;
             if (j < nv)
               pub_tile[nt * npub * m0 + r * nv + j] = *reinterpret_cast<const uint16_t *>(W.pub + 64u * r + 2u * j);

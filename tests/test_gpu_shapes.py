@@ -9,6 +9,7 @@ import numpy as np
 import pytest
 import torch
 
+import oracle
 import synth
 
 sf = pytest.importorskip("paper_1512_02951_amd")
@@ -98,6 +99,29 @@ def test_every_launch_shape_gives_the_default_fragments(prec, shape, mask):
         _forget(shape, mask, prec)
     assert tried >= 6
     assert int(status.item()) == 0
+
+
+@pytest.mark.parametrize("prec", ["fp16", "bf16"])
+@pytest.mark.parametrize("mask", [(1 << 40) - 1, (1 << 63) - 1])
+def test_quantiser_operands_of_small_workgroups(prec, mask):
+    # 40 and 63 private positions: three and four quantiser passes, 192 and 256
+    # operands, which workgroups of one and two waves fill in several rounds
+    shape = C, H, W = 3, 72, 136
+    x = synth.image(H, W, C, 3, 8).cuda()
+    key, c0 = synth.aes_key(3), synth.ctr0(3, 8)
+    got = {}
+    try:
+        for w in (1, 2, 4):
+            for which in ("frag", "defrag"):
+                sf.set_launch_shape(shape, mask, which, w, 1, precision=prec)
+            got[w] = sf.frag_image(x, mask, key, c0, precision=prec)
+            assert torch.equal(sf.defrag_image(got[w], key, c0), x), w
+    finally:
+        _forget(shape, mask, prec)
+    ref = oracle.frag(x.cpu().numpy(), mask, key, c0)
+    for w, f in got.items():
+        assert np.array_equal(f.private.cpu().numpy()[:ref["cipher"].size], ref["cipher"]), w
+        _same(f, got[1], w)
 
 
 @pytest.mark.parametrize("prec,shape,mask", [("fp32", (3, 520, 264), sf.prefix_mask(5)),
