@@ -114,19 +114,23 @@ inline bool plain_heavy(const Geom &g) { return g.npriv >= 8; }
 // whatever the workgroup): 2 wavefronts per workgroup, so that the tiles
 // spread over more compute units.  At 1024^2, DC + 9 AC (one tile per CU):
 // FP32 frag 10.4 us with 4 waves, 9.3 with 2, defrag 8.6 / 7.5; bf16 frag 14.7
-// with 8, 11.9 with 2, defrag 11.6 / 8.2.  The line: FP32 at four per CU (2048 x
-// 2040) is slower with 2 (round trip 20.3 / 21.1), the precision frag at six
-// (2056 x 3000) is not faster (16.0 / 16.5), its defrag there still is
-// (13.3 / 11.9).
-inline bool small_image(const DeviceState &ds, const Geom &g, int which) {
-  const uint32_t per_cu = g.precision == SF_FP32 ? 2u : which == 0 ? 4u : 8u;
+// with 8, 11.9 with 2, defrag 11.6 / 8.2.  The lines, by round trips: FP32 at two
+// per CU 18.1 us with 4 waves, 16.3 with 2, at four per CU (2048 x 2040) 20.3 /
+// 21.1; fp16 DC + 9 AC at four per CU 24.5 with 8, 21.1 with 2.  Precision defrag
+// with 2 (frag with 8) is faster alone up to six per CU, but the round trip
+// is slower from five on (every workgroup fills its own tables): at five
+// fp16 24.6 with 8, 25.0 with 2, without a cipher 16.9 / 18.6; at 2056 x 3000
+// (5.9 per CU) bf16 26.5 / 26.8, without a cipher 20.4 / 21.3 (selections of
+// more than 15 positions lose up to 2 % there).
+inline bool small_image(const DeviceState &ds, const Geom &g) {
+  const uint32_t per_cu = g.precision == SF_FP32 ? 2u : 4u;
   return g.ntiles <= per_cu * (uint32_t)ds.num_cu;
 }
 // Default waves per workgroup of the plain kernels: frag 4 (one tile each,
 // up to 5 resident per SIMD by registers and LDS), defrag 4 from 8 private
 // coefficients on, else 2; small images 2.
 inline uint32_t plain_default_waves(const DeviceState &ds, const Geom &g, int which) {
-  return (which == 0 || plain_heavy(g)) && !small_image(ds, g, which) ? 4u : 2u;
+  return (which == 0 || plain_heavy(g)) && !small_image(ds, g) ? 4u : 2u;
 }
 
 // Launchers (plain.hip, aes.hip).

@@ -69,6 +69,22 @@ def test_default_shapes():
         assert sf.launch_shape(big, sf.prefix_mask(9), which, precision="fp16") == (8, 1)
 
 
+@pytest.mark.parametrize("prec,mask,above", [("fp32", sf.prefix_mask(5), ((4, 0), (2, 0))),
+                                             ("fp32", sf.prefix_mask(9), ((4, 0), (4, 1))),
+                                             ("fp16", sf.prefix_mask(9), ((8, 1), (8, 1))),
+                                             ("bf16", sf.prefix_mask(9), ((8, 1), (8, 1)))])
+def test_default_shapes_of_small_images(prec, mask, above):
+    """At most 2 waves per workgroup up to 2 (FP32) or 4 (reduced precision)
+    tiles per compute unit, in both directions; the form's own default beyond."""
+    limit = (2 if prec == "fp32" else 4) * torch.cuda.get_device_properties(0).multi_processor_count
+    for tiles in (1, limit, limit + 1, 2 * limit):
+        shape = (1, 8 * tiles, 512)  # a tile of 64 blocks per row of blocks
+        _forget(shape, mask, prec)
+        for which, (waves, resident) in zip(("frag", "defrag"), above):
+            expect = (min(waves, 2) if tiles <= limit else waves, resident)
+            assert sf.launch_shape(shape, mask, which, precision=prec) == expect, (tiles, which)
+
+
 @pytest.mark.parametrize("prec,shape,mask", CASES)
 def test_every_launch_shape_gives_the_default_fragments(prec, shape, mask):
     C, H, W = shape
