@@ -129,9 +129,9 @@ __device__ __forceinline__ void sha512_round(uint64_t (&v)[8], uint64_t kw) {
 // the bit length in the last word.  Returns the digest words H[0..7].
 // Rounds 0..15 are unrolled (most message words are constants there), and
 // rounds 16..31 (most terms of their schedule words are zero or constant; with
-// them in the loop, a 4096^2 RGB round trip took 189 us, now 174); rounds 32..79 run as a loop of 16 unrolled
-// rounds that extends the schedule in place, which keeps the code and the live
-// schedule words small.
+// them in the loop, a 4096^2 RGB round trip took 189 us, now 174); rounds
+// 32..79 run as a loop of 16 unrolled rounds that extends the schedule in
+// place, which keeps the code and the live schedule words small.
 template <int NP>
 __device__ __forceinline__ void sha512_private(const int32_t (&q)[kPixMaxPriv], uint32_t np_rt, uint64_t (&Hout)[8]) {
   const uint32_t np = NP > 0 ? (uint32_t)NP : np_rt;
@@ -234,8 +234,14 @@ __device__ __forceinline__ uint32_t tile_bytes(const PixArgs &a, uint32_t t) {
 // NP > 0: "DC + (NP - 1) AC" selection resolved at compile time; NP = 0: any
 // selection of at most kPixMaxPriv coefficients (a.nat, a.np).  The private
 // AC integers come from the int8 matrix-core quantiser (at most 16 AC).
+// Strong level: registers for 3 waves per SIMD, no more waves.  With as many as
+// LDS allows (5, 97 registers) the rounds are scheduled one dependent
+// instruction after another: 4096^2 RGB, DC + 5 AC 98.8 us, 89.0 so (2 waves
+// 93.6); DC + 14 AC 124.7, 115.0 (134.0).  defrag has nothing to gain (84.0, 84.6,
+// 90.4).
 template <int NP, bool kStrong>
-__global__ __launch_bounds__(kThreads) void pixel_frag_kernel(PixArgs a) {
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kStrong ? 3 : 1, kStrong ? 3 : 8)))
+void pixel_frag_kernel(PixArgs a) {
   using MP = std::conditional_t<(NP > 0), MaskPrefix<NP>, MaskRuntime>;
   __shared__ AesLds s_aes;
   __shared__ __attribute__((aligned(16))) uint8_t s_bits[kWaves][kPixRegion];
@@ -245,12 +251,12 @@ __global__ __launch_bounds__(kThreads) void pixel_frag_kernel(PixArgs a) {
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   // the first tile's pixels are in flight while the tables arrive (see AesFill)
   const TileGeom &g = a.g;
-  uint32_t t = blockIdx.x * kWaves + wave;
+  const uint32_t t = blockIdx.x * kWaves + wave;
   AesFill fill;
   const int first = wave == 0u ? private_ac<MP>(g.mask, lane) : -1;
   fill.load(a.aes_t0, a.aes.key, threadIdx.x);
   const Q2Operands q2op = q2_operands(a.q2, first, lane);
-  TileLane L = tile_lane(g, min(t, g.ntiles - 1u), lane);
+  const TileLane L = tile_lane(g, min(t, g.ntiles - 1u), lane);
   uint32_t xs[16];
   load_block(g, L, xs);
   __builtin_amdgcn_sched_barrier(0);
@@ -266,85 +272,78 @@ __global__ __launch_bounds__(kThreads) void pixel_frag_kernel(PixArgs a) {
   const uint32_t npair = (np + 1u) / 2u;
   const uint32_t dc = NP > 0 ? 1u : (uint32_t)(g.mask & 1u);
   constexpr int kNPair = NP > 0 ? (NP + 1) / 2 : 0;
-  while (t < g.ntiles) {
-    const bool valid = L.valid != 0u;
-    const cu32_ptr inv = inv_table();
-    for (uint32_t i = lane; i < kPixRegion / 16u; i += 64u) reinterpret_cast<uint4 *>(lp)[i] = make_uint4(0, 0, 0, 0);
-    uint32_t S = 0;
+  if (t >= g.ntiles) return;  // one tile per wave
+  const bool valid = L.valid != 0u;
+  const cu32_ptr inv = inv_table();
+  for (uint32_t i = lane; i < kPixRegion / 16u; i += 64u) reinterpret_cast<uint4 *>(lp)[i] = make_uint4(0, 0, 0, 0);
+  uint32_t S = 0;
 #pragma unroll
-    for (int w = 0; w < 16; ++w) S = __builtin_amdgcn_udot4(xs[w], 0x01010101u, S, false);
-    uint32_t xsg[16];
+  for (int w = 0; w < 16; ++w) S = __builtin_amdgcn_udot4(xs[w], 0x01010101u, S, false);
+  uint32_t xsg[16];
 #pragma unroll
-    for (int w = 0; w < 16; ++w) xsg[w] = xs[w] ^ 0x80808080u;  // samples - 128 as signed bytes
-    q2_mfma(xsg, lane, stage, s_q2[lane]);
-    wave_lds_sync();
+  for (int w = 0; w < 16; ++w) xsg[w] = xs[w] ^ 0x80808080u;  // samples - 128 as signed bytes
+  q2_mfma(xsg, lane, stage, s_q2[lane]);
+  wave_lds_sync();
 
-    int32_t q[kPixMaxPriv];
+  int32_t q[kPixMaxPriv];
 #pragma unroll
-    for (int j = 0; j < kPixMaxPriv; ++j) {
-      q[j] = 0;
-      if (NP > 0 ? j < NP : (uint32_t)j < np) {
-        const int n = NP > 0 ? kZigZag.nat[j < 64 ? j : 0] : (int)a.nat[j];
-        if (n == 0) q[j] = (int32_t)((S + 3u + ((S >> 3) & 1u)) >> 3);  // round half even of S / 8
-        else q[j] = q2_round(q2_mfma_acc(stage, (uint32_t)j - dc, lane));
-      }
-    }
-    // the public part uses the exact integers (packed in pairs for the
-    // inverse); the fields and the strong-level hash hold the stored ones
-    uint32_t qp[kPixMaxPriv / 2];
-#pragma unroll
-    for (int i = 0; i < kPixMaxPriv / 2; ++i) qp[i] = ((uint32_t)q[2 * i] & 0xffffu) | ((uint32_t)q[2 * i + 1] << 16);
-    const int32_t lim = (1 << a.ac_bits) - 1;  // never reached at 10 bits (|AC| <= 1020)
-#pragma unroll
-    for (int j = 0; j < kPixMaxPriv; ++j) {
+  for (int j = 0; j < kPixMaxPriv; ++j) {
+    q[j] = 0;
+    if (NP > 0 ? j < NP : (uint32_t)j < np) {
       const int n = NP > 0 ? kZigZag.nat[j < 64 ? j : 0] : (int)a.nat[j];
-      if (n != 0) q[j] = max(-lim, min(lim, q[j]));
-    }
-    // fields into the tile's bit stream (zeroed above)
-    if (valid) {
-      const uint32_t base = (uint32_t)lane * a.rec_bits;
-      const uint32_t acw = a.ac_bits + 1u;
-#pragma unroll
-      for (int j = 0; j < kPixMaxPriv; ++j) {
-        if (NP > 0 ? j < NP : (uint32_t)j < np) {
-          const int n = NP > 0 ? kZigZag.nat[j < 64 ? j : 0] : (int)a.nat[j];
-          const uint32_t mag = (uint32_t)(q[j] < 0 ? -q[j] : q[j]);
-          const uint32_t fld = n == 0 ? (uint32_t)q[j] : (mag | (q[j] < 0 ? 1u << a.ac_bits : 0u));
-          const uint32_t pos = base + field_offset((uint32_t)j, dc, acw);
-          const uint64_t v = (uint64_t)fld << (pos & 31u);
-          atomicOr(&lw[pos >> 5], (uint32_t)v);
-          if ((uint32_t)(v >> 32)) atomicOr(&lw[(pos >> 5) + 1u], (uint32_t)(v >> 32));
-        }
-      }
-    }
-    uint64_t Hm[8];
-    if constexpr (kStrong) sha512_private<NP>(q, np, Hm);
-    if (valid) {
-      uint8_t *dst = a.pub + L.org;
-#pragma unroll
-      for (int y = 0; y < 8; ++y) {
-        uint32_t rlo, rhi;
-        recon_row<kNPair>(inv, qp, npair, y, rlo, rhi);
-        uint32_t plo = bytes_sub(xs[2 * y], rlo), phi = bytes_sub(xs[2 * y + 1], rhi);
-        if constexpr (kStrong) {
-          uint32_t mlo, mhi;
-          row_mask(Hm[y], mlo, mhi);
-          plo ^= mlo;
-          phi ^= mhi;
-        }
-        __builtin_nontemporal_store(((uint64_t)phi << 32) | plo, reinterpret_cast<uint64_t *>(dst + (size_t)y * g.W));
-      }
-    }
-    wave_lds_sync();
-    tile_ctr_store(lp, a.priv + (uint64_t)t * a.stride, tile_bytes(a, t), lane, s_aes, a.aes.enabled, a.aes.ctr_hi,
-                   a.aes.ctr_lo, (uint64_t)t * (a.stride / 16u));
-    wave_lds_sync();
-    t += gridDim.x * kWaves;
-    if (t < g.ntiles) {
-      L = tile_lane(g, t, lane);
-      load_block(g, L, xs);
+      if (n == 0) q[j] = (int32_t)((S + 3u + ((S >> 3) & 1u)) >> 3);  // round half even of S / 8
+      else q[j] = q2_round(q2_mfma_acc(stage, (uint32_t)j - dc, lane));
     }
   }
+  // the public part uses the exact integers (packed in pairs for the
+  // inverse); the fields and the strong-level hash hold the stored ones
+  uint32_t qp[kPixMaxPriv / 2];
+#pragma unroll
+  for (int i = 0; i < kPixMaxPriv / 2; ++i) qp[i] = ((uint32_t)q[2 * i] & 0xffffu) | ((uint32_t)q[2 * i + 1] << 16);
+  const int32_t lim = (1 << a.ac_bits) - 1;  // never reached at 10 bits (|AC| <= 1020)
+#pragma unroll
+  for (int j = 0; j < kPixMaxPriv; ++j) {
+    const int n = NP > 0 ? kZigZag.nat[j < 64 ? j : 0] : (int)a.nat[j];
+    if (n != 0) q[j] = max(-lim, min(lim, q[j]));
+  }
+  // fields into the tile's bit stream (zeroed above)
+  if (valid) {
+    const uint32_t base = (uint32_t)lane * a.rec_bits;
+    const uint32_t acw = a.ac_bits + 1u;
+#pragma unroll
+    for (int j = 0; j < kPixMaxPriv; ++j) {
+      if (NP > 0 ? j < NP : (uint32_t)j < np) {
+        const int n = NP > 0 ? kZigZag.nat[j < 64 ? j : 0] : (int)a.nat[j];
+        const uint32_t mag = (uint32_t)(q[j] < 0 ? -q[j] : q[j]);
+        const uint32_t fld = n == 0 ? (uint32_t)q[j] : (mag | (q[j] < 0 ? 1u << a.ac_bits : 0u));
+        const uint32_t pos = base + field_offset((uint32_t)j, dc, acw);
+        const uint64_t v = (uint64_t)fld << (pos & 31u);
+        atomicOr(&lw[pos >> 5], (uint32_t)v);
+        if ((uint32_t)(v >> 32)) atomicOr(&lw[(pos >> 5) + 1u], (uint32_t)(v >> 32));
+      }
+    }
+  }
+  uint64_t Hm[8];
+  if constexpr (kStrong) sha512_private<NP>(q, np, Hm);
+  if (valid) {
+    uint8_t *dst = a.pub + L.org;
+#pragma unroll
+    for (int y = 0; y < 8; ++y) {
+      uint32_t rlo, rhi;
+      recon_row<kNPair>(inv, qp, npair, y, rlo, rhi);
+      uint32_t plo = bytes_sub(xs[2 * y], rlo), phi = bytes_sub(xs[2 * y + 1], rhi);
+      if constexpr (kStrong) {
+        uint32_t mlo, mhi;
+        row_mask(Hm[y], mlo, mhi);
+        plo ^= mlo;
+        phi ^= mhi;
+      }
+      __builtin_nontemporal_store(((uint64_t)phi << 32) | plo, reinterpret_cast<uint64_t *>(dst + (size_t)y * g.W));
+    }
+  }
+  wave_lds_sync();
+  tile_ctr_store(lp, a.priv + (uint64_t)t * a.stride, tile_bytes(a, t), lane, s_aes, a.aes.enabled, a.aes.ctr_hi,
+                 a.aes.ctr_lo, (uint64_t)t * (a.stride / 16u));
 }
 
 // The lane's public rows (lanes without a block read the image's first).
@@ -365,10 +364,10 @@ __global__ __launch_bounds__(kThreads) void pixel_defrag_kernel(PixArgs a) {
   const int lane = threadIdx.x & 63;
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const TileGeom &g = a.g;
-  uint32_t t = blockIdx.x * kWaves + wave;
+  const uint32_t t = blockIdx.x * kWaves + wave;
   AesFill fill;
   fill.load(a.aes_t0, a.aes.key, threadIdx.x);
-  TileLane L = tile_lane(g, min(t, g.ntiles - 1u), lane);
+  const TileLane L = tile_lane(g, min(t, g.ntiles - 1u), lane);
   uint32_t pw[16];
   pixel_load_public(a, L, pw);
   __builtin_amdgcn_sched_barrier(0);
@@ -380,64 +379,60 @@ __global__ __launch_bounds__(kThreads) void pixel_defrag_kernel(PixArgs a) {
   const uint32_t npair = (np + 1u) / 2u;
   const uint32_t dc = NP > 0 ? 1u : (uint32_t)(g.mask & 1u);
   constexpr int kNPair = NP > 0 ? (NP + 1) / 2 : 0;
-  while (t < g.ntiles) {
-    const bool valid = L.valid != 0u;
-    // the public rows are in flight during the decryption
-    tile_ctr_load(lp, a.priv + (uint64_t)t * a.stride, tile_bytes(a, t), lane, s_aes, a.aes.enabled, a.aes.ctr_hi,
-                  a.aes.ctr_lo, (uint64_t)t * (a.stride / 16u));
-    wave_lds_sync();
-    int32_t q[kPixMaxPriv];
-    const uint32_t base = (uint32_t)lane * a.rec_bits;
-    const uint32_t acw = a.ac_bits + 1u;
+  if (t >= g.ntiles) return;  // one tile per wave
+  const bool valid = L.valid != 0u;
+  // the public rows are in flight during the decryption
+  tile_ctr_load(lp, a.priv + (uint64_t)t * a.stride, tile_bytes(a, t), lane, s_aes, a.aes.enabled, a.aes.ctr_hi,
+                a.aes.ctr_lo, (uint64_t)t * (a.stride / 16u));
+  wave_lds_sync();
+  int32_t q[kPixMaxPriv];
+  const uint32_t base = (uint32_t)lane * a.rec_bits;
+  const uint32_t acw = a.ac_bits + 1u;
 #pragma unroll
-    for (int j = 0; j < kPixMaxPriv; ++j) {
-      q[j] = 0;
-      if (NP > 0 ? j < NP : (uint32_t)j < np) {
-        const int n = NP > 0 ? kZigZag.nat[j < 64 ? j : 0] : (int)a.nat[j];
-        const uint32_t pos = base + field_offset((uint32_t)j, dc, acw);
-        const uint64_t v = (uint64_t)lw[pos >> 5] | ((uint64_t)lw[(pos >> 5) + 1u] << 32);
-        const uint32_t raw = (uint32_t)(v >> (pos & 31u));
-        const int32_t mag = (int32_t)(raw & ((1u << a.ac_bits) - 1u));
-        const int32_t val = n == 0 ? (int32_t)(raw & 0x7ffu) : (((raw >> a.ac_bits) & 1u) ? -mag : mag);
-        q[j] = valid ? val : 0;
-      }
+  for (int j = 0; j < kPixMaxPriv; ++j) {
+    q[j] = 0;
+    if (NP > 0 ? j < NP : (uint32_t)j < np) {
+      const int n = NP > 0 ? kZigZag.nat[j < 64 ? j : 0] : (int)a.nat[j];
+      const uint32_t pos = base + field_offset((uint32_t)j, dc, acw);
+      const uint64_t v = (uint64_t)lw[pos >> 5] | ((uint64_t)lw[(pos >> 5) + 1u] << 32);
+      const uint32_t raw = (uint32_t)(v >> (pos & 31u));
+      const int32_t mag = (int32_t)(raw & ((1u << a.ac_bits) - 1u));
+      const int32_t val = n == 0 ? (int32_t)(raw & 0x7ffu) : (((raw >> a.ac_bits) & 1u) ? -mag : mag);
+      q[j] = valid ? val : 0;
     }
-    wave_lds_sync();
-    uint32_t qp[kPixMaxPriv / 2];
+  }
+  wave_lds_sync();
+  uint32_t qp[kPixMaxPriv / 2];
 #pragma unroll
-    for (int i = 0; i < kPixMaxPriv / 2; ++i) qp[i] = ((uint32_t)q[2 * i] & 0xffffu) | ((uint32_t)q[2 * i + 1] << 16);
-    uint64_t Hm[8];
-    if constexpr (kStrong) sha512_private<NP>(q, np, Hm);
-    const cu32_ptr inv = inv_table();
-    if (valid) {
-      uint8_t *dst = a.pix_out + L.org;
+  for (int i = 0; i < kPixMaxPriv / 2; ++i) qp[i] = ((uint32_t)q[2 * i] & 0xffffu) | ((uint32_t)q[2 * i + 1] << 16);
+  uint64_t Hm[8];
+  if constexpr (kStrong) sha512_private<NP>(q, np, Hm);
+  const cu32_ptr inv = inv_table();
+  if (valid) {
+    uint8_t *dst = a.pix_out + L.org;
 #pragma unroll
-      for (int y = 0; y < 8; ++y) {
-        uint32_t plo = pw[2 * y], phi = pw[2 * y + 1];
-        if constexpr (kStrong) {
-          uint32_t mlo, mhi;
-          row_mask(Hm[y], mlo, mhi);
-          plo ^= mlo;
-          phi ^= mhi;
-        }
-        uint32_t rlo, rhi;
-        recon_row<kNPair>(inv, qp, npair, y, rlo, rhi);
-        const uint32_t xlo = bytes_add(plo, rlo), xhi = bytes_add(phi, rhi);
-        __builtin_nontemporal_store(((uint64_t)xhi << 32) | xlo, reinterpret_cast<uint64_t *>(dst + (size_t)y * g.W));
+    for (int y = 0; y < 8; ++y) {
+      uint32_t plo = pw[2 * y], phi = pw[2 * y + 1];
+      if constexpr (kStrong) {
+        uint32_t mlo, mhi;
+        row_mask(Hm[y], mlo, mhi);
+        plo ^= mlo;
+        phi ^= mhi;
       }
-    }
-    t += gridDim.x * kWaves;
-    if (t < g.ntiles) {
-      L = tile_lane(g, t, lane);
-      pixel_load_public(a, L, pw);
+      uint32_t rlo, rhi;
+      recon_row<kNPair>(inv, qp, npair, y, rlo, rhi);
+      const uint32_t xlo = bytes_add(plo, rlo), xhi = bytes_add(phi, rhi);
+      __builtin_nontemporal_store(((uint64_t)xhi << 32) | xlo, reinterpret_cast<uint64_t *>(dst + (size_t)y * g.W));
     }
   }
 }
 
-int pix_grid(uint32_t ntiles) {
-  const uint64_t need = ((uint64_t)ntiles + kWaves - 1) / kWaves;
-  return (int)(need < 0x7fffffffu ? need : 0x7fffffffu);
-}
+// One tile per wave (an image holds at most 2^20).  A loop over the tiles that
+// no launch ever ran twice, with the next tile's loads at its end, cost the
+// kernels up to 100 registers (without it: 97 for frag, 87 or 114-127 strong for
+// defrag): round trips of 4096^2 RGB, strong DC + 14 AC 254 us with it, 226
+// without, first level DC + 3 AC 68.5 / 57.7, DC + 5 AC 56.1 / 54.7.
+int pix_grid(uint32_t ntiles) { return (int)((ntiles + kWaves - 1u) / kWaves); }
 
 // Prefix selections with a compile-time variant: DC + 2, 5 or 9 AC.
 int static_np(uint64_t mask) {
