@@ -487,15 +487,17 @@ __device__ __forceinline__ double dpp_f64(double v) {
 constexpr int kQuadXor1 = 0xB1, kQuadXor2 = 0x4E, kRowRor4 = 0x124, kRowRor8 = 0x128;
 
 // Sum over the 16 lanes of a row of four values per lane; lane f gets the
-// total of value f % 4 (the additions of each total are the same in every
-// lane that gets it, up to the order of two operands).
+// total of value f % 4.  The quads' sums Q0 .. Q3 are added by 8 lanes first,
+// then by 4: (Qa + Qa+2) + (Qb + Qb+2) in every quad, the same bits up to the
+// order of two operands (by 4 first, quads 0 and 2 would add Q0 + Q3, quads 1
+// and 3 Q0 + Q1).
 __device__ __forceinline__ double row_sum_quad(const double (&v)[4], int lane) {
   const bool b1 = lane & 2, b0 = lane & 1;
   const double k0 = (b1 ? v[2] : v[0]) + dpp_f64<kQuadXor2>(b1 ? v[0] : v[2]);
   const double k1 = (b1 ? v[3] : v[1]) + dpp_f64<kQuadXor2>(b1 ? v[1] : v[3]);
   double t = (b0 ? k1 : k0) + dpp_f64<kQuadXor1>(b0 ? k0 : k1);
-  t += dpp_f64<kRowRor4>(t);
   t += dpp_f64<kRowRor8>(t);
+  t += dpp_f64<kRowRor4>(t);
   return t;
 }
 
@@ -628,8 +630,8 @@ __global__ __launch_bounds__(kTuneThreads) void sm_tune_kernel(LossArgs a, float
     if (f == 0 && (row & 1) == 0) part[wave][64 + (row >> 1)] = rdw;
     ms += dpp_f64<kQuadXor1>(ms);
     ms += dpp_f64<kQuadXor2>(ms);
-    ms += dpp_f64<kRowRor4>(ms);
     ms += dpp_f64<kRowRor8>(ms);
+    ms += dpp_f64<kRowRor4>(ms);
     __syncthreads();
     double dm = -((part[0][n] + part[1][n]) + (part[2][n] + part[3][n]));
     if (n == 0) dm += (part[0][65] + part[1][65]) + (part[2][65] + part[3][65]);

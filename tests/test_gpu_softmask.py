@@ -274,6 +274,25 @@ def test_tuner_at_the_edges_of_its_groups_of_64_images(B):
     assert mask == oracle.harden(lt.cpu().numpy(), 6)
 
 
+@pytest.mark.parametrize("B", [1, 65, 129, 257])
+def test_tuner_lanes_use_one_sum_of_the_mask(B):
+    # logits whose masks are 1, twice 0.9 * 2^-53 and next to nothing: their sum is
+    # 1 or 1 + 2^-52 by the order of the additions.  With that budget and a large
+    # weight the difference decides over a whole step, so frequencies 20 and 40,
+    # alike in everything, stay alike only if all lanes have the same sum.
+    stats = torch.ones((B, 65), dtype=torch.float64)
+    stats[:, 0], stats[:, 64] = 16.0, 32.0  # 8 x 8 images of mean 1/2
+    l0 = np.full(64, -100.0, np.float32)
+    l0[1], l0[20], l0[40] = 50.0, -36.8425, -36.8425
+    sd, ld = stats.cuda(), _dev(l0)
+    mask = torch.zeros(1, dtype=torch.int64, device="cuda")
+    sf.check(sm.lib().sf_softmask_tune(sd.data_ptr(), B, 8, 8, 1e30, 1.0, 1, 0.05, ld.data_ptr(), None,
+                                       mask.data_ptr(), 1, sf._stream(None)))
+    got = ld.cpu().numpy()
+    assert got[20] == got[40]
+    assert got[1] == l0[1] and int(mask.item()) == 1 << 1
+
+
 def test_shape_errors():
     x = torch.zeros((1, 12, 16), dtype=torch.float32, device="cuda")
     with pytest.raises(sf.SefragError) as e:
