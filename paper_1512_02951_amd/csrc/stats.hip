@@ -449,7 +449,8 @@ __device__ __forceinline__ uint32_t joint_bytes(const uint32_t (&c)[4], uint32_t
 }
 
 __global__ __launch_bounds__(kJointThreads) void stats_joint_kernel(JointArgs a) {
-  __shared__ uint32_t s_bins[kHalfBins];
+  __shared__ __attribute__((aligned(16))) uint32_t s_bins[kHalfBins];
+  static_assert(__alignof__(s_bins) >= sizeof(uint4), "read 16 bytes at a time below");
   for (uint32_t i = threadIdx.x; i < kHalfBins; i += kJointThreads) s_bins[i] = 0u;
   __syncthreads();
   const uint64_t v0 = (uint64_t)blockIdx.x * a.per_chunk;
@@ -673,7 +674,8 @@ __global__ __launch_bounds__(kFinThreads) void stats_rows_kernel(FinArgs a) {
   const uint32_t j = blockIdx.x;
   // the row's counts: four bins a word, every fourth workgroup's a thread
   // (at most 64 x 255 in a halfword)
-  __shared__ uint32_t s_c[4][256];
+  __shared__ __attribute__((aligned(16))) uint32_t s_c[4][256];
+  static_assert(__alignof__(s_c) >= sizeof(uint4), "written 16 bytes at a time below");
   uint32_t even = 0, odd = 0;
   const uint32_t *rowp = reinterpret_cast<const uint32_t *>(a.bytes) + 64u * j + (t & 63);
   for (uint32_t p = (uint32_t)t >> 6; p < a.nbytes; p += 64u) {
