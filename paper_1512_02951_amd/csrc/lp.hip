@@ -749,42 +749,43 @@ __global__ __launch_bounds__(512, lp_waves_per_eu<BF>()) void lp_frag_kernel(LpA
             clo[s] = make_uint4(lw[0], lw[1], lw[2], lw[3]);
             has_lo[s] = BF && ((rs.any >> (8 * s)) & 0xffu) != 0u;
           });
-        } else
-        static_for<0, 4>([&](auto sc) {
-          constexpr int s = decltype(sc)::value, mt = s / 2, sg = s % 2;
-          uint32_t hw[4], lw[4];
-          bool any_lo = false;
-          static_for<0, 4>([&](auto pc) {
-            constexpr int pr = decltype(pc)::value;
-            constexpr int r0 = 8 * sg + 2 * pr;  // slots r0, r0 + 1 of M-tile mt
-            uint32_t w = pack16<BF>(acc[mt][r0], acc[mt][r0 + 1]);
-            uint32_t lo = 0u;
-            static_for<0, 2>([&](auto ec) {
-              constexpr int e = decltype(ec)::value, r = r0 + e;
-              const Pair<MP> P(32 * mt + 8 * (r / 4) + (r % 4), h);
-              if (P.any_priv) {
-                const int32_t q = (int32_t) * reinterpret_cast<const int16_t *>(stage + P.priv_off(jb, h));
-                uint32_t qh, ql;
-                split_int<BF>(q, qh, ql);
-                if (P.mine_priv) {
-                  w = e ? ((w & 0x0000ffffu) | (qh << 16)) : ((w & 0xffff0000u) | qh);
-                  lo |= ql << (16 * e);
+        } else {
+          static_for<0, 4>([&](auto sc) {
+            constexpr int s = decltype(sc)::value, mt = s / 2, sg = s % 2;
+            uint32_t hw[4], lw[4];
+            bool any_lo = false;
+            static_for<0, 4>([&](auto pc) {
+              constexpr int pr = decltype(pc)::value;
+              constexpr int r0 = 8 * sg + 2 * pr;  // slots r0, r0 + 1 of M-tile mt
+              uint32_t w = pack16<BF>(acc[mt][r0], acc[mt][r0 + 1]);
+              uint32_t lo = 0u;
+              static_for<0, 2>([&](auto ec) {
+                constexpr int e = decltype(ec)::value, r = r0 + e;
+                const Pair<MP> P(32 * mt + 8 * (r / 4) + (r % 4), h);
+                if (P.any_priv) {
+                  const int32_t q = (int32_t) * reinterpret_cast<const int16_t *>(stage + P.priv_off(jb, h));
+                  uint32_t qh, ql;
+                  split_int<BF>(q, qh, ql);
+                  if (P.mine_priv) {
+                    w = e ? ((w & 0x0000ffffu) | (qh << 16)) : ((w & 0xffff0000u) | qh);
+                    lo |= ql << (16 * e);
+                  }
+                  any_lo = true;
                 }
-                any_lo = true;
-              }
-              if (P.any_pub && !P.mine_priv) {
-                const uint16_t v = bv ? (uint16_t)(e ? (w >> 16) : w) : (uint16_t)0;
-                *reinterpret_cast<uint16_t *>(W.pub + (P.both_pub ? 64u * P.c0.rank + (2u * jl + 256u * h)
-                                                                  : 64u * P.c1.rank + 2u * jl)) = v;
-              }
+                if (P.any_pub && !P.mine_priv) {
+                  const uint16_t v = bv ? (uint16_t)(e ? (w >> 16) : w) : (uint16_t)0;
+                  *reinterpret_cast<uint16_t *>(W.pub + (P.both_pub ? 64u * P.c0.rank + (2u * jl + 256u * h)
+                                                                    : 64u * P.c1.rank + 2u * jl)) = v;
+                }
+              });
+              hw[pr] = w;
+              lw[pr] = lo;
             });
-            hw[pr] = w;
-            lw[pr] = lo;
+            chi[s] = make_uint4(hw[0], hw[1], hw[2], hw[3]);
+            clo[s] = make_uint4(lw[0], lw[1], lw[2], lw[3]);
+            has_lo[s] = BF && any_lo;
           });
-          chi[s] = make_uint4(hw[0], hw[1], hw[2], hw[3]);
-          clo[s] = make_uint4(lw[0], lw[1], lw[2], lw[3]);
-          has_lo[s] = BF && any_lo;
-        });
+        }
 
         // ---- reconstruction and residual codes
         f32x16 y[2];
@@ -1075,12 +1076,21 @@ __global__ __launch_bounds__(512, lp_waves_per_eu<BF>()) void lp_defrag_kernel(L
 
 // ---------------------------------------------------------------------------
 // launchers
-// Dynamic LDS of a workgroup: `shared` (the rank table of selections known at
-// run time; frag: the quantiser's B operands) plus `per_wave` for each wavefront (private stages; frag: also the public
-// stage of one half).
-bool compiled_selection(uint64_t mask) {
-  return mask == (1ull << 2) - 1 || mask == (1ull << 3) - 1 || mask == (1ull << 6) - 1 || mask == (1ull << 10) - 1;
+// Calls f with the selection's type: the one list of the compiled selections.
+template <class F>
+auto with_selection(uint64_t mask, F &&f) {
+  switch (mask) {
+    case (1ull << 2) - 1: return f(MaskPrefix<2>{});
+    case (1ull << 3) - 1: return f(MaskPrefix<3>{});
+    case (1ull << 6) - 1: return f(MaskPrefix<6>{});
+    case (1ull << 10) - 1: return f(MaskPrefix<10>{});
+    default: return f(MaskRuntime{});
+  }
 }
+
+// Dynamic LDS of a workgroup: `shared` (the rank table of selections known at
+// run time; frag: the quantiser's B operands) plus `per_wave` for each
+// wavefront (private stages; frag: also the public stage of one half).
 struct LpLdsPlan {
   size_t fixed, shared, per_wave;
 };
@@ -1088,7 +1098,8 @@ LpLdsPlan lp_lds_plan(const Geom &g, int which) {
   const uint32_t npass = (g.npriv + 15u) / 16u, pstride = (2u * g.npriv * 64u + 15u) & ~15u;
   LpLdsPlan p;
   p.fixed = sizeof(AesLds) + (g.precision == SF_BF16 ? sizeof(LpLds<true>) : sizeof(LpLds<false>));
-  p.shared = (compiled_selection(g.mask) ? 0u : sizeof(RankTable)) + (which == 0 ? 64u * npass * sizeof(LpQ2) : 0u);
+  p.shared = with_selection(g.mask, [](auto mp) { return kRankBytes<decltype(mp)>; }) +
+             (which == 0 ? 64u * npass * sizeof(LpQ2) : 0u);
   p.per_wave = (size_t)(which == 0 ? kFragGroup : kDefragGroup) * pstride + (which == 0 ? (size_t)64u * g.npub : 0u);
   return p;
 }
@@ -1123,14 +1134,7 @@ int launch(const DeviceState &ds, const LpArgs &a0, const Shape &sh, const LpLds
 
 template <bool BF, bool kFrag>
 int dispatch(const DeviceState &ds, const LpArgs &a, const Shape &sh, const LpLdsPlan &p, hipStream_t stream) {
-  auto go = [&](auto mp) { return launch<BF, decltype(mp), kFrag>(ds, a, sh, p, stream); };
-  switch (a.g.mask) {
-    case (1ull << 2) - 1: return go(MaskPrefix<2>{});
-    case (1ull << 3) - 1: return go(MaskPrefix<3>{});
-    case (1ull << 6) - 1: return go(MaskPrefix<6>{});
-    case (1ull << 10) - 1: return go(MaskPrefix<10>{});
-    default: return go(MaskRuntime{});
-  }
+  return with_selection(a.g.mask, [&](auto mp) { return launch<BF, decltype(mp), kFrag>(ds, a, sh, p, stream); });
 }
 
 // The resolved shape, or SF_ENOTSUP if its LDS does not fit a workgroup.
