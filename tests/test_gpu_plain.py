@@ -195,6 +195,26 @@ def test_encrypt_private_with_workgroup_wide_tables(nbytes, low):
     assert np.array_equal(out.cpu().numpy(), data)
 
 
+@pytest.mark.parametrize("carry,bits", [(3572, 16), (20000, 64), (8512 * 3 - 1, 64), (1 << 20, 64)])
+def test_encrypt_private_reuses_and_rebuilds_the_upper_counter(carry, bits):
+    # 33 MiB + 5: on 256 compute units each workgroup takes a run of 8512 blocks,
+    # 8 or 9 for a thread, over which what the counter's upper bits give is kept.
+    # The low `bits` bits carry at block `carry`: within a pass in the middle of a
+    # run (3572 = 3 * 1024 + 500, 20000 = 2 * 8512 + 2 * 1024 + 928), at a run's last
+    # block, and far on; then the kept values serve again.
+    nbytes = (33 << 20) + 5
+    rng = np.random.default_rng(carry)
+    key = rng.integers(0, 256, 16, dtype=np.uint8).tobytes()
+    low = (0x123456789ABC << 16 if bits == 16 else 0) + (1 << bits) - carry
+    ctr0 = bytes(7) + b"\x02" + low.to_bytes(8, "big")
+    data = rng.integers(0, 256, nbytes, dtype=np.uint8)
+    d = torch.from_numpy(data).cuda()
+    out = sf.encrypt_private(key, ctr0, d)
+    assert np.array_equal(out.cpu().numpy(), oracle.ctr_xor(key, ctr0, data))
+    sf.encrypt_private(key, ctr0, out, out=out)  # in place, decrypt
+    assert np.array_equal(out.cpu().numpy(), data)
+
+
 def test_published_ctr_vector_on_gpu():
     from conftest import golden
     rows = golden("sp800_38a_ctr_aes128.txt")
