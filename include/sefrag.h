@@ -207,8 +207,8 @@ typedef struct sf_launch_shape {
                                coefficients, else 2; reduced precision: the
                                largest that lets two workgroups share a
                                compute unit's LDS; at most 2 for images of
-                               up to 2 (FP32) or 4 (reduced precision)
-                               tiles per compute unit)                  */
+                               up to 2 tiles per compute unit, in reduced
+                               precision 4 for frag and 6 for defrag)     */
   uint32_t resident;        /* 1: one resident generation of workgroups
                                (as many as the device holds at once) loops
                                over the tiles (the default of the reduced

@@ -1196,7 +1196,7 @@ uint32_t lp_default_waves(const DeviceState &ds, const Geom &g, int which) {
       const size_t b = lp_lds_bytes(g, which, w);
       if (b > ds.max_lds_per_block) continue;
       if (pass == 0 && 2 * b > cu_lds) continue;
-      return small_image(ds, g) && w > 2u ? 2u : w;
+      return small_image(ds, g, which) && w > 2u ? 2u : w;
     }
   return 0;
 }

@@ -116,21 +116,20 @@ inline bool plain_heavy(const Geom &g) { return g.npriv >= 8; }
 // FP32 frag 10.4 us with 4 waves, 9.3 with 2, defrag 8.6 / 7.5; bf16 frag 14.7
 // with 8, 11.9 with 2, defrag 11.6 / 8.2.  The lines, by round trips: FP32 at two
 // per CU 18.1 us with 4 waves, 16.3 with 2, at four per CU (2048 x 2040) 20.3 /
-// 21.1; fp16 DC + 9 AC at four per CU 24.5 with 8, 21.1 with 2.  Precision defrag
-// with 2 (frag with 8) is faster alone up to six per CU, but the round trip
-// is slower from five on (every workgroup fills its own tables): at five
-// fp16 24.6 with 8, 25.0 with 2, without a cipher 16.9 / 18.6; at 2056 x 3000
-// (5.9 per CU) bf16 26.5 / 26.8, without a cipher 20.4 / 21.3 (selections of
-// more than 15 positions lose up to 2 % there).
-inline bool small_image(const DeviceState &ds, const Geom &g) {
-  const uint32_t per_cu = g.precision == SF_FP32 ? 2u : 4u;
+// 21.1.  Precision frag: fp16 DC + 9 AC at four per CU 24.5 with 8, 21.1 with 2; at
+// six (2056 x 3000) not faster alone (16.0 / 16.5).  Precision defrag, DC + 9 AC
+// with 8 waves / with 2: at six bf16 26.5 / 26.0, fp16 25.5 / 25.6, at seven (2048 x
+// 3584) 26.0 / 27.4 and 25.1 / 26.4, every workgroup filling its own tables;
+// without a cipher the 8 win from five on (fp16 DC + 5 AC 17.3 / 18.3).
+inline bool small_image(const DeviceState &ds, const Geom &g, int which) {
+  const uint32_t per_cu = g.precision == SF_FP32 ? 2u : which == 0 ? 4u : 6u;
   return g.ntiles <= per_cu * (uint32_t)ds.num_cu;
 }
 // Default waves per workgroup of the plain kernels: frag 4 (one tile each,
 // up to 5 resident per SIMD by registers and LDS), defrag 4 from 8 private
 // coefficients on, else 2; small images 2.
 inline uint32_t plain_default_waves(const DeviceState &ds, const Geom &g, int which) {
-  return (which == 0 || plain_heavy(g)) && !small_image(ds, g) ? 4u : 2u;
+  return (which == 0 || plain_heavy(g)) && !small_image(ds, g, which) ? 4u : 2u;
 }
 
 // Launchers (plain.hip, aes.hip).

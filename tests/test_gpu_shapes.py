@@ -74,13 +74,14 @@ def test_default_shapes():
                                              ("fp16", sf.prefix_mask(9), ((8, 1), (8, 1))),
                                              ("bf16", sf.prefix_mask(9), ((8, 1), (8, 1)))])
 def test_default_shapes_of_small_images(prec, mask, above):
-    """At most 2 waves per workgroup up to 2 (FP32) or 4 (reduced precision)
-    tiles per compute unit, in both directions; the form's own default beyond."""
-    limit = (2 if prec == "fp32" else 4) * torch.cuda.get_device_properties(0).multi_processor_count
-    for tiles in (1, limit, limit + 1, 2 * limit):
-        shape = (1, 8 * tiles, 512)  # a tile of 64 blocks per row of blocks
-        _forget(shape, mask, prec)
-        for which, (waves, resident) in zip(("frag", "defrag"), above):
+    """At most 2 waves per workgroup up to 2 tiles per compute unit (FP32), or 4
+    for frag and 6 for defrag (reduced precision); the form's own default beyond."""
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    for which, (waves, resident), per_cu in zip(("frag", "defrag"), above, (2, 2) if prec == "fp32" else (4, 6)):
+        limit = per_cu * cus
+        for tiles in (1, limit, limit + 1, 2 * limit):
+            shape = (1, 8 * tiles, 512)  # a tile of 64 blocks per row of blocks
+            _forget(shape, mask, prec)
             expect = (min(waves, 2) if tiles <= limit else waves, resident)
             assert sf.launch_shape(shape, mask, which, precision=prec) == expect, (tiles, which)
 
