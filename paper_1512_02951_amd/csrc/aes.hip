@@ -60,8 +60,8 @@ __global__ __launch_bounds__(kThreads) void ctr_kernel(CtrArgs a) {
 // rounds (14 and 8 of 16 lookups) is kept from block to block and made again
 // when they do change.  138 lookups of 2 cycles and about 250 vector
 // instructions (1 cycle each over the CU's four SIMDs) are left per 64 blocks,
-// so both units are busy.  Measured on 128 MiB in and out: 202 -> 88 us (42 ->
-// 95 G blocks/s).
+// so both units are busy.  Measured on 128 MiB in and out: 202 -> 88-93 us (42 ->
+// 90-95 G blocks/s).
 constexpr int kWideThreads = 1024;
 typedef uint32_t WideTables[2][256][64];
 

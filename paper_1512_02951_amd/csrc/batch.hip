@@ -10,9 +10,10 @@
 //                       (plain_tile.h) on every global tile, with the
 //                       geometry, selection, fragments and counter block of
 //                       the tile's image.  Two schedules:
-//                       work queue (the default of very large plans): a
-//                       kernel clears a counter, then each wave grabs
-//                       tiles_per_grab consecutive tiles per atomic.
+//                       work queue (the default of very large plans, and of
+//                       frag of large ones with selections known at run
+//                       time): a kernel clears a counter, then each wave
+//                       grabs tiles_per_grab consecutive tiles per atomic.
 //                       static chunks (the default of all others): the
 //                       global tiles are cut into chunks of
 //                       4 * tiles_per_grab consecutive tiles, dealt

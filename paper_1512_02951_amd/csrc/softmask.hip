@@ -467,7 +467,7 @@ __global__ __launch_bounds__(64) void sm_loss_kernel(LossArgs a, const float *lo
 // All orders are fixed, so every lane, wave and run gets the same bits.
 // Measured on 64 images of 1024^2 and 200 steps, the statistics pass
 // included: 2 120 us with one wave and the statistics in LDS (10 us a step),
-// 356 us so (1.5 us a step).
+// 352 us so (1.5 us a step).
 constexpr int kTuneWaves = 4;
 constexpr int kTuneThreads = 64 * kTuneWaves;
 constexpr uint32_t kTuneGroup = 16 * kTuneWaves;  // images per group

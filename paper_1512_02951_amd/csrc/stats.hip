@@ -4,7 +4,7 @@
 // block entropy (h = 8), correlation of adjacent samples, two-dimensional
 // correlation, bit difference and PSNR.
 //
-// Three kernels, every moment an exact integer:
+// Four kernels, every moment an exact integer:
 //  * band kernel: one wavefront per band of 8 rows x 32 blocks of a plane;
 //    lanes k and k + 32 hold rows 0-3 and 4-7 of block k (8 bytes a row, and
 //    the row below).  Pair products with v_dot4_u32_u8 on the words and their
@@ -16,18 +16,20 @@
 //    LDS byte counters (256 per block, four to a word, ds_add), then the product
 //    of every sample's value count; H = 6 - log2(product) / 64.  Per-workgroup
 //    partial sums.  It also clears the histogram for the next kernel.  Bound by
-//    vector issue (about 990 instructions for a band of both images): 94 -> 66
+//    vector issue (about 990 instructions for a band of both images): 94 -> 60
 //    us on 4096^2 RGB since the counters have no bank conflicts, each sample
 //    takes 9 instead of 16 instructions, one logarithm serves both images and
-//    the registers leave room for 4 waves per SIMD.
+//    4 waves share a SIMD (at 4 spilled registers: the next band's rows, loaded
+//    ahead for straight-line code, gained nothing by themselves).
 //  * joint histogram: a workgroup counts a chunk of samples in 65536 16-bit LDS
 //    counters (128 KB; bins b and b + 32768 share a word) and leaves the low
 //    bytes of its counts in the workspace; the few counts above 255 go to the
 //    global histogram by atomics, as do counters near their limit between
 //    parts of the chunk.  32-bit counters of half the bins read the images
 //    twice and added every bin by an atomic of its own: 47 us on 4096^2 RGB, 13
-//    of them the 8.4 M atomics (about one per L2 channel and clock); now 29, and
-//    the rows kernel 13 instead of 8.
+//    of them the 8.4 M atomics (about one per L2 channel and clock); now 28, and
+//    the rows kernel 13 instead of 8.  A workspace too small for the counts
+//    gets all of them by atomics (a call 150 us instead of 110).
 //  * rows (256 workgroups) and finalize (one workgroup): reduce the partials
 //    and the histogram in fixed orders, then form the histograms, entropies,
 //    NMI, chi-square and correlations in FP64.
